@@ -40,7 +40,7 @@ using leet::kChunk;
 // workgroups exist (one per compute unit of a 256-CU device measured best), but no segment is
 // shorter than a minimum number of chunks: each extra segment costs one D x DV fp32 state written,
 // scanned and re-read, and every segment but the last has its K and V read twice.  The fp32
-// kernel is bound by MFMA latency per chunk, not by HBM, so it takes much shorter segments.
+// kernel is bound by its matrix work per chunk, not by HBM, so it takes much shorter segments.
 constexpr int kTargetWorkgroups = 256;
 constexpr int kMinSegChunksF32 = 2;
 constexpr int kMaxDevices = 64;
@@ -66,7 +66,14 @@ struct Plan {
     int pre_split;  // the pre-pass and the scan run on segments this many times finer than the walk's
     size_t ws_bytes;
     bool coop;  // the column-split kernel runs this call
+    bool fold;  // no scan: the walk combines the pre-pass states itself
 };
+
+// fp32: a walk workgroup that enters segment s after s pre-pass states can read and combine those
+// states itself, which saves the scan kernel's launch and its pass over all states.  It pays while a
+// workgroup has at most this much to read: 3 states at d = 128 (B1 H32 N256: 26.2 -> 23.4 us; 7 states,
+// B1 H32 N512: 31.5 -> 36.3), 15 at d = 64 (3 states: 14.1 -> 12.7, 15 states, B2 H8 N2048: 27.4 -> 26.3).
+constexpr size_t kFoldBytes = (size_t)240 << 10;
 
 // The pre-pass is a pure read stream and runs faster with two workgroups per compute unit
 // (config 4: 6.2 against 4.7 TB/s), the walk does not (more boundary states to carry); so the
@@ -76,12 +83,12 @@ int wide_pre_split(long BH, int nseg, int seg_chunks) {
     return (nseg > 1 && seg_chunks >= 16 && seg_chunks % 2 == 0 && BH * (nseg - 1) <= 256) ? 2 : 1;
 }
 
-// The fp32 pre-pass is bound by fp32 MFMA issue, so what counts is how evenly its workgroups fill
+// The fp32 pre-pass is bound by its matrix work too, so what counts is how evenly its workgroups fill
 // the 256 compute units: it runs on segments `split` times finer than the walk's, with the split
 // (1, 2, 4 or 8 parts of at least two chunks) that needs the fewest chunk-times -- rounds of 256
 // workgroups x chunks per workgroup, a tenth less once two workgroups share a compute unit and
-// overlap -- plus half a chunk-time per part for the longer scan (B4 H16 N4096 d128 in fp32: 192
-// workgroups of 16 chunks take 93 us, 384 of 8 chunks 85 us, 768 of 4 chunks 73 us).
+// overlap -- plus half a chunk-time per part for the longer scan (B4 H16 N4096 d128, whole call:
+// 223 us with 1 part, 219 with 2, 222 with 4; B1 H128 N8192 d64: 422, 368, 355).
 int f32_pre_split(long BH, int nseg, int seg_chunks) {
     if (nseg <= 1) return 1;
     const long units = BH * (nseg - 1);
@@ -182,6 +189,7 @@ bool make_plan(long BH, int N, int D, int DV, int dtype, int segments, int choic
         // one state per boundary the pre-pass computes, and, with segments, one more per sequence:
         // the scan's copy of the entering state, which the walk reads instead of the caller's buffer
         const size_t slots = nseg > 1 ? (size_t)(nseg - 1) * plan->pre_split + 1 : 0;
+        plan->fold = dtype == LEET_F32 && plan->pre_split == 1 && (size_t)(nseg - 1) * D * DV * sizeof(float) <= kFoldBytes;
         plan->ws_bytes = (size_t)BH * slots * D * DV * sizeof(float);
         return true;
     };
@@ -394,15 +402,16 @@ int forward_impl(const void* q, const void* k, const void* v, const float* gamma
 
     leet::FwdParams p;
     p.q = q; p.k = k; p.v = v; p.gamma = gamma; p.out = out;
-    p.state_in = state_in; p.state_out = state_out;
+    p.state_in = state_in; p.state_out = state_out; p.state_copy = nullptr;
     p.seg_state = static_cast<float*>(ws);
     p.H = H; p.N = N; p.nseg = plan.nseg; p.seg_chunks = plan.seg_chunks;
     p.state_slots = (plan.nseg - 1) * plan.pre_split;
     p.state_step = plan.pre_split;
-    // With segments, the first segments of the walk read the entering state from the scan's copy
-    // of it (the slots after all boundary states), never from the caller's buffer: state_out may
-    // alias state_in, and the last segment of a sequence may finish, and write it, before the
-    // first segment of the same sequence has started.
+    p.fold = plan.fold ? 1 : 0;
+    // With segments, the first segments of the walk read the entering state from the copy of it that
+    // the scan (with fold the pre-pass) makes (the slots after all boundary states), never from the
+    // caller's buffer: state_out may alias state_in, and the last segment of a sequence may finish,
+    // and write it, before the first segment of the same sequence has started.
     float* state_copy = nullptr;
     if (plan.nseg > 1 && state_in) {
         state_copy = p.seg_state + (size_t)BH * p.state_slots * d * dv;
@@ -415,17 +424,20 @@ int forward_impl(const void* q, const void* k, const void* v, const float* gamma
     leet::FwdParams pre = p;  // geometry of the pre-pass and of the scan
     pre.nseg = p.state_slots + 1;
     pre.seg_chunks = plan.seg_chunks / plan.pre_split;
+    pre.state_in = state_in;
+    pre.state_copy = state_copy;
     const bool in16 = dtype != LEET_F32;
     const bool f16 = dtype == LEET_F16;
     const bool out16 = out_dtype != LEET_F32;
 
     const bool coop = plan.coop;
     auto launch_states = [&]() {
-        return coop   ? leet::launch_fwd_16bit_coop_states(p, (int)BH, d, dv, f16, s)
+        return coop   ? leet::launch_fwd_16bit_coop_states(pre, (int)BH, d, dv, f16, s)
                : in16 ? leet::launch_fwd_16bit_states(pre, (int)BH, d, dv, f16, s)
                       : leet::launch_fwd_f32_states(pre, (int)BH, d, s);
     };
     auto launch_scan = [&]() {
+        if (plan.fold) return hipSuccess;
         return leet::launch_seg_scan(p.seg_state, state_in, state_copy, gamma, (int)BH, H, pre.nseg, pre.seg_chunks * kChunk,
                                      p.state_step, d, dv, s);
     };
