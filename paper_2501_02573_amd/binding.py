@@ -171,12 +171,24 @@ def _check_dev(*tensors: Optional[torch.Tensor]) -> torch.device:
     return dev
 
 
-def _stream_ptr(dev: torch.device) -> int:
-    return torch.cuda.current_stream(dev).cuda_stream
-
-
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# What a short call costs is its host time (a decode step of one user: 3.8 us on the GPU, 13.7 us a call
+# with a device guard, a Stream object and a c_void_p per argument; 9.1 us as below): the device
+# guard is entered only where it would change the device, the stream is taken as the raw handle, and
+# addresses travel as plain integers.
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
+def _call(fn, dev: torch.device, *args) -> int:
+    """fn(*args, the device's current stream) with ``dev`` current; returns the status."""
+    index = dev.index
+    if index == torch.cuda.current_device():
+        return fn(*args, _raw_stream(index))
+    with torch.cuda.device(dev):
+        return fn(*args, _raw_stream(index))
 
 
 KERNEL_WIDE, KERNEL_COLUMN_SPLIT, KERNEL_AUTO = 0, 1, 2
@@ -250,12 +262,11 @@ def leet_attn_forward(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, gamma: 
                       out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Chunked prefill with zero initial state; returns fp32 ``out`` [B, H, N, d]."""
     if out is None:
-        out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
+        out = torch.empty_like(q, dtype=torch.float32)
     B, H, N, d = _check_forward(q, k, v, gamma, out)
     dev = _check_dev(q, k, v, gamma, out)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_forward(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), B, H, N, d,
-                                   _dtype_code(q), ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_forward, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), B, H, N, d,
+               _dtype_code(q))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_forward")
     return out
@@ -267,7 +278,7 @@ def leet_attn_forward_ex(q, k, v, gamma, out: Optional[torch.Tensor] = None,
                          workspace: Optional[torch.Tensor] = None, segments: int = 0) -> torch.Tensor:
     """Chunked prefill with state hand-off and optional caller-owned workspace."""
     if out is None:
-        out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
+        out = torch.empty_like(q, dtype=torch.float32)
     B, H, N, d = _check_forward(q, k, v, gamma, out)
     for name, s in (("state_in", state_in), ("state_out", state_out)):
         if s is not None and (s.dtype != torch.float32 or tuple(s.shape) != (B, H, d, d)):
@@ -278,10 +289,9 @@ def leet_attn_forward_ex(q, k, v, gamma, out: Optional[torch.Tensor] = None,
             raise TypeError("workspace must be a uint8 tensor")
         ws_bytes = workspace.numel()
     dev = _check_dev(q, k, v, gamma, out, state_in, state_out, workspace)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_forward_ex(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
-                                      _ptr(state_out), _ptr(workspace), ws_bytes, int(segments),
-                                      B, H, N, d, _dtype_code(q), ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_forward_ex, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
+               _ptr(state_out), _ptr(workspace), ws_bytes, int(segments),
+               B, H, N, d, _dtype_code(q))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_forward_ex")
     return out
@@ -299,7 +309,7 @@ def leet_attn_forward_v2(q, k, v, gamma: Optional[torch.Tensor], out: Optional[t
     ``mask=LEET_MASK_CAUSAL``.  Unsupported combinations are reported by the library.
     """
     if out is None:
-        out = torch.empty(q.shape, dtype=out_dtype or torch.float32, device=q.device)
+        out = torch.empty_like(q, dtype=out_dtype or torch.float32)
     B, H, N, d = _check_forward(q, k, v, gamma, out, any_out_dtype=True)
     for name, s in (("state_in", state_in), ("state_out", state_out)):
         if s is not None and (s.dtype != torch.float32 or tuple(s.shape) != (B, H, d, d)):
@@ -310,11 +320,9 @@ def leet_attn_forward_v2(q, k, v, gamma: Optional[torch.Tensor], out: Optional[t
             raise TypeError("workspace must be a uint8 tensor")
         ws_bytes = workspace.numel()
     dev = _check_dev(q, k, v, gamma, out, state_in, state_out, workspace)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_forward_v2(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
-                                      _ptr(state_out), _ptr(workspace), ws_bytes, int(segments),
-                                      B, H, N, d, _dtype_code(q), _dtype_code(out), int(mask),
-                                      ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_forward_v2, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
+               _ptr(state_out), _ptr(workspace), ws_bytes, int(segments),
+               B, H, N, d, _dtype_code(q), _dtype_code(out), int(mask))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_forward_v2")
     return out
@@ -326,16 +334,14 @@ def leet_attn_forward_recurrent(q, k, v, gamma: Optional[torch.Tensor], out: Opt
                                 mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """Row-based (token-by-token) prefill on the GPU: the comparison point for the chunked path."""
     if out is None:
-        out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
+        out = torch.empty_like(q, dtype=torch.float32)
     B, H, N, d = _check_forward(q, k, v, gamma, out)
     for name, s in (("state_in", state_in), ("state_out", state_out)):
         if s is not None and (s.dtype != torch.float32 or tuple(s.shape) != (B, H, d, d)):
             raise ValueError(f"{name} must be float32 [B, H, d, d]")
     dev = _check_dev(q, k, v, gamma, out, state_in, state_out)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_forward_recurrent(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
-                                             _ptr(state_out), B, H, N, d, _dtype_code(q), int(mask),
-                                             ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_forward_recurrent, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
+               _ptr(state_out), B, H, N, d, _dtype_code(q), int(mask))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_forward_recurrent")
     return out
@@ -344,14 +350,14 @@ def leet_attn_forward_recurrent(q, k, v, gamma: Optional[torch.Tensor], out: Opt
 def leet_attn_forward_profile(q, k, v, gamma, out: Optional[torch.Tensor] = None, segments: int = 0):
     """One prefill with per-kernel HIP-event timing; returns (out, [pre-pass ms, scan ms, walk ms])."""
     if out is None:
-        out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
+        out = torch.empty_like(q, dtype=torch.float32)
     B, H, N, d = _check_forward(q, k, v, gamma, out)
     dev = _check_dev(q, k, v, gamma, out)
     ms = (ctypes.c_float * 3)()
     with torch.cuda.device(dev):
         st = lib.leet_attn_forward_profile(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), None, None,
                                            None, 0, int(segments), B, H, N, d, _dtype_code(q),
-                                           ctypes.c_void_p(_stream_ptr(dev)), ms)
+                                           _raw_stream(dev.index), ms)
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_forward_profile")
     return out, [float(x) for x in ms]
@@ -362,9 +368,7 @@ def calibration_stream(mode: str, src: Optional[torch.Tensor], dst: torch.Tensor
     """Launches the plain copy / read / fill kernel over ``nbytes`` (measurement aid)."""
     code = {"copy": 0, "read": 1, "fill": 2, "copy_nt": 3, "fill_nt": 4}[mode]
     dev = _check_dev(src, dst)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_calibration_stream(code, _ptr(src), _ptr(dst), int(nbytes), int(workgroups),
-                                              ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_calibration_stream, dev, code, _ptr(src), _ptr(dst), int(nbytes), int(workgroups))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_calibration_stream")
 
@@ -389,12 +393,11 @@ def leet_attn_decode_step(q, k, v, gamma, state, out: Optional[torch.Tensor] = N
     if q.dtype != torch.bfloat16:
         raise TypeError("leet_attn_decode_step takes bfloat16 q, k, v (use leet_attn_decode_step_ex for float32)")
     if out is None:
-        out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
+        out = torch.empty_like(q, dtype=torch.float32)
     B, H, d = _check_decode(q, k, v, gamma, state, out)
     dev = _check_dev(q, k, v, gamma, state, out)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_decode_step(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
-                                       B, H, d, ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_decode_step, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
+               B, H, d)
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_decode_step")
     return out
@@ -403,12 +406,11 @@ def leet_attn_decode_step(q, k, v, gamma, state, out: Optional[torch.Tensor] = N
 def leet_attn_decode_step_ex(q, k, v, gamma, state, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """One decode step with float32 or bfloat16 q, k, v."""
     if out is None:
-        out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
+        out = torch.empty_like(q, dtype=torch.float32)
     B, H, d = _check_decode(q, k, v, gamma, state, out)
     dev = _check_dev(q, k, v, gamma, state, out)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_decode_step_ex(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
-                                          B, H, d, _dtype_code(q), ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_decode_step_ex, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
+               B, H, d, _dtype_code(q))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_decode_step_ex")
     return out
@@ -418,12 +420,11 @@ def leet_attn_decode_step_v2(q, k, v, gamma: Optional[torch.Tensor], state, out:
                              mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """One decode step with float32, bfloat16 or float16 q, k, v and either mask."""
     if out is None:
-        out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
+        out = torch.empty_like(q, dtype=torch.float32)
     B, H, d = _check_decode(q, k, v, gamma, state, out)
     dev = _check_dev(q, k, v, gamma, state, out)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_decode_step_v2(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
-                                          B, H, d, _dtype_code(q), int(mask), ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_decode_step_v2, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
+               B, H, d, _dtype_code(q), int(mask))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_decode_step_v2")
     return out
@@ -460,7 +461,7 @@ def leet_attn_forward_rd(q, k, v, gamma: Optional[torch.Tensor], out: Optional[t
                          out_dtype: Optional[torch.dtype] = None, mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """Chunked prefill with q, k of width r and v, out of width dv; states are [B, H, r, dv]."""
     if out is None:
-        out = torch.empty(v.shape, dtype=out_dtype or torch.float32, device=v.device)
+        out = torch.empty_like(v, dtype=out_dtype or torch.float32)
     B, H, N, r, dv = _check_rd(q, k, v, gamma, out, True)
     _check_states_rd(B, H, r, dv, state_in=state_in, state_out=state_out)
     ws_bytes = 0
@@ -469,11 +470,9 @@ def leet_attn_forward_rd(q, k, v, gamma: Optional[torch.Tensor], out: Optional[t
             raise TypeError("workspace must be a uint8 tensor")
         ws_bytes = workspace.numel()
     dev = _check_dev(q, k, v, gamma, out, state_in, state_out, workspace)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_forward_rd(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
-                                      _ptr(state_out), _ptr(workspace), ws_bytes, int(segments),
-                                      B, H, N, r, dv, _dtype_code(q), _dtype_code(out), int(mask),
-                                      ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_forward_rd, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
+               _ptr(state_out), _ptr(workspace), ws_bytes, int(segments),
+               B, H, N, r, dv, _dtype_code(q), _dtype_code(out), int(mask))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_forward_rd")
     return out
@@ -486,7 +485,7 @@ def leet_attn_forward_v3(q, k, v, gamma: Optional[torch.Tensor], out: Optional[t
                          out_dtype: Optional[torch.dtype] = None, mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """``leet_attn_forward_rd`` with the kernel choice given per call."""
     if out is None:
-        out = torch.empty(v.shape, dtype=out_dtype or torch.float32, device=v.device)
+        out = torch.empty_like(v, dtype=out_dtype or torch.float32)
     B, H, N, r, dv = _check_rd(q, k, v, gamma, out, True)
     _check_states_rd(B, H, r, dv, state_in=state_in, state_out=state_out)
     ws_bytes = 0
@@ -495,11 +494,9 @@ def leet_attn_forward_v3(q, k, v, gamma: Optional[torch.Tensor], out: Optional[t
             raise TypeError("workspace must be a uint8 tensor")
         ws_bytes = workspace.numel()
     dev = _check_dev(q, k, v, gamma, out, state_in, state_out, workspace)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_forward_v3(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
-                                      _ptr(state_out), _ptr(workspace), ws_bytes, int(segments), int(kernel),
-                                      B, H, N, r, dv, _dtype_code(q), _dtype_code(out), int(mask),
-                                      ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_forward_v3, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
+               _ptr(state_out), _ptr(workspace), ws_bytes, int(segments), int(kernel),
+               B, H, N, r, dv, _dtype_code(q), _dtype_code(out), int(mask))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_forward_v3")
     return out
@@ -529,14 +526,14 @@ class PreparedForward:
         self._args = (_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in), _ptr(state_out),
                       _ptr(workspace), ws_bytes, int(segments), int(kernel), B, H, N, r, dv,
                       _dtype_code(q), _dtype_code(out), int(mask))
-        self._stream = None if stream is None else ctypes.c_void_p(stream)
+        self._stream = None if stream is None else int(stream)
         self._fn = lib.leet_attn_forward_v3
         self.out = out
 
     def __call__(self) -> torch.Tensor:
         if torch.cuda.current_device() != self._dev.index:
             raise ValueError("PreparedForward called with another device current")
-        stream = self._stream if self._stream is not None else ctypes.c_void_p(torch.cuda.current_stream(self._dev).cuda_stream)
+        stream = self._stream if self._stream is not None else _raw_stream(self._dev.index)
         st = self._fn(*self._args, stream)
         if st != LEET_OK:
             raise LeetAttnError(st, "leet_attn_forward_v3")
@@ -572,10 +569,8 @@ def leet_attn_forward_static(q, k, v, gamma, out: torch.Tensor, state_in: Option
         if s is not None and (s.dtype != torch.float32 or tuple(s.shape) != (B, H, d, d)):
             raise ValueError(f"{name} must be float32 [B, H, d, d]")
     dev = _check_dev(q, k, v, gamma, out, state_in, state_out)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_forward_static(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
-                                          _ptr(state_out), int(segments), B, H, N, d, _dtype_code(q),
-                                          ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_forward_static, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
+               _ptr(state_out), int(segments), B, H, N, d, _dtype_code(q))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_forward_static")
     return out
@@ -587,14 +582,12 @@ def leet_attn_forward_recurrent_rd(q, k, v, gamma: Optional[torch.Tensor], out: 
                                    mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """Row-based prefill with q, k of width r and v, out of width dv."""
     if out is None:
-        out = torch.empty(v.shape, dtype=torch.float32, device=v.device)
+        out = torch.empty_like(v, dtype=torch.float32)
     B, H, N, r, dv = _check_rd(q, k, v, gamma, out, False)
     _check_states_rd(B, H, r, dv, state_in=state_in, state_out=state_out)
     dev = _check_dev(q, k, v, gamma, out, state_in, state_out)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_forward_recurrent_rd(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
-                                                _ptr(state_out), B, H, N, r, dv, _dtype_code(q), int(mask),
-                                                ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_forward_recurrent_rd, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out),
+               _ptr(state_in), _ptr(state_out), B, H, N, r, dv, _dtype_code(q), int(mask))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_forward_recurrent_rd")
     return out
@@ -606,14 +599,12 @@ def leet_attn_forward_fleet(q, k, v, gamma: Optional[torch.Tensor], out: Optiona
                             mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """FleetAttention prefill (rank-sum of discounted cumulative sums); q, k [B, H, N, r], v [B, H, N, dv]."""
     if out is None:
-        out = torch.empty(v.shape, dtype=torch.float32, device=v.device)
+        out = torch.empty_like(v, dtype=torch.float32)
     B, H, N, r, dv = _check_rd(q, k, v, gamma, out, False)
     _check_states_rd(B, H, r, dv, state_in=state_in, state_out=state_out)
     dev = _check_dev(q, k, v, gamma, out, state_in, state_out)
-    with torch.cuda.device(dev):
-        st = lib.leet_attn_forward_fleet(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
-                                         _ptr(state_out), B, H, N, r, dv, _dtype_code(q), int(mask),
-                                         ctypes.c_void_p(_stream_ptr(dev)))
+    st = _call(lib.leet_attn_forward_fleet, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in),
+               _ptr(state_out), B, H, N, r, dv, _dtype_code(q), int(mask))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_forward_fleet")
     return out
@@ -632,21 +623,19 @@ def leet_attn_decode_step_rd(q, k, v, gamma: Optional[torch.Tensor], state, out:
     B, H, r = q.shape
     dv = v.shape[2]
     if out is None:
-        out = torch.empty(v.shape, dtype=torch.float32, device=v.device)
+        out = torch.empty_like(v, dtype=torch.float32)
     if gamma is not None and (gamma.dtype != torch.float32 or gamma.numel() != H):
         raise ValueError("gamma must be float32 with one value per head")
     _check_states_rd(B, H, r, dv, state=state)
     if out.dtype != torch.float32 or tuple(out.shape) != (B, H, dv):
         raise ValueError("out must be float32 [B, H, dv]")
     dev = _check_dev(q, k, v, gamma, state, out)
-    with torch.cuda.device(dev):
-        if store is None:
-            st = lib.leet_attn_decode_step_rd(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
-                                              B, H, r, dv, _dtype_code(q), int(mask), ctypes.c_void_p(_stream_ptr(dev)))
-        else:
-            st = lib.leet_attn_decode_step_v3(_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
-                                              B, H, r, dv, _dtype_code(q), int(mask), int(store),
-                                              ctypes.c_void_p(_stream_ptr(dev)))
+    if store is None:
+        st = _call(lib.leet_attn_decode_step_rd, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
+                   B, H, r, dv, _dtype_code(q), int(mask))
+    else:
+        st = _call(lib.leet_attn_decode_step_v3, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
+                   B, H, r, dv, _dtype_code(q), int(mask), int(store))
     if st != LEET_OK:
         raise LeetAttnError(st, "leet_attn_decode_step_v3" if store is not None else "leet_attn_decode_step_rd")
     return out

@@ -247,6 +247,27 @@ bool make_plan(long BH, int N, int D, int DV, int dtype, int segments, int choic
     return finish(false, nseg, seg_chunks);
 }
 
+// make_plan for the calls themselves, with the last plan of the calling thread kept: pricing the
+// candidates takes about as long as a launch, and a program's calls mostly repeat one shape.
+bool call_plan(long BH, int N, int D, int DV, int dtype, int segments, int choice, Plan* plan) {
+    if (choice == LEET_CHOICE_DEFAULT) choice = g_bf16_kernel.load(std::memory_order_relaxed);
+    struct Kept {
+        long BH = 0;  // 0: nothing kept
+        int N, D, DV, dtype, segments, choice;
+        Plan plan;
+    };
+    static thread_local Kept kept;
+    if (kept.BH != BH || kept.N != N || kept.D != D || kept.DV != DV || kept.dtype != dtype || kept.segments != segments ||
+        kept.choice != choice) {
+        kept.BH = 0;
+        if (!make_plan(BH, N, D, DV, dtype, segments, choice, &kept.plan)) return false;
+        kept.BH = BH; kept.N = N; kept.D = D; kept.DV = DV;
+        kept.dtype = dtype; kept.segments = segments; kept.choice = choice;
+    }
+    *plan = kept.plan;
+    return true;
+}
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // d: width of q and k rows; dv: width of v and out rows.  Square shapes for every type; rank 128 with
@@ -379,7 +400,7 @@ int forward_impl(const void* q, const void* k, const void* v, const float* gamma
     if (N == 0) return empty_forward(state_in, state_out, BH, d, dv, stream, kernel_ms);
 
     Plan plan;
-    if (!make_plan(BH, N, d, dv, dtype, segments, kernel_choice, &plan)) return LEET_ERR_TOO_LARGE;
+    if (!call_plan(BH, N, d, dv, dtype, segments, kernel_choice, &plan)) return LEET_ERR_TOO_LARGE;
     if (ws_kind == kWsStatic && plan.ws_bytes > kStaticScratchBytes) return LEET_ERR_SCRATCH_LIMIT;
     int dev = 0;
     status = current_device(&dev);
