@@ -45,7 +45,7 @@
 // the compute waves run, and the only thing that ties the two together is one workgroup
 // barrier per chunk.  The chunk is software-pipelined over that barrier: in iteration t the row
 // waves produce O(t), the state waves S(t+1), the store waves write chunk t-1 to memory, and
-// the loaders write chunk t+1 to LDS and issue the loads of chunk t+3.  The K tile, S^T and the
+// the loaders write chunk t+1 to LDS and issue the loads of chunk t+3 (t+4 with three stages).  The K tile, S^T and the
 // output tiles are double-buffered in LDS, the V slice and its scaled copy triple-buffered.
 //
 // MFMA conventions (32x32x16): an A (B) operand holds, in lane l, row (column) l%32 and the
@@ -128,10 +128,14 @@ __device__ __forceinline__ f32x16 zero16() {
 
 // kOut = true : full walk (outputs + state).   kOut = false : state only (segment pre-pass).
 // E: ElemBf16 or ElemF16 (input type).  kOut16: outputs in the input type instead of fp32.
-// Two loader waves with two register stages each: more of either measured no faster (four waves,
-// three stages), the loads are bound by what one compute unit keeps in flight, not by issue.
+// Two loader waves (four measured no faster) with two or three register stages each.  Over inputs that
+// come from memory the loads are bound by what a compute unit keeps in flight, so a third stage pays
+// where it costs nothing else: at D = 64, whose chunks are half the bytes (B8 H16 N4000 70.8 -> 67.7 us with
+// fp32 and 62.9 -> 61.4 with fp16 outputs, B1 H16 N16000 59.9 -> 55.8), and a little at value width 256
+// (B1 H32 N2000 40.6 -> 40.2).  D = DV = 128 keeps two: its row waves fill the registers (B2 H16 N2048 29.1
+// against 29.7, B1 H32 N777 13.9 against 14.1).  Four spill at D = 128 and gain nothing more at 64.
 constexpr int kCoopLoaderWaves = 2;
-constexpr int kCoopStages = 2;
+constexpr int coop_stages(int D, int DV) { return D == 64 || DV == 256 ? 3 : 2; }
 constexpr int kCoopThreads = 384 + 64 * kCoopLoaderWaves;
 
 // D: width of q and k rows (rank); DV: width of v and out rows (DV / 32 slices per sequence).
@@ -141,7 +145,7 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     auto mfma32 = [](u32x4 a, u32x4 b, f32x16 c) { return E::mfma32(a, b, c); };
     constexpr int NT = kCoopThreads;            // two row waves, two state waves, two store waves and the loader waves
     constexpr int NL = 64 * kCoopLoaderWaves;   // loader threads (waves 6 and up)
-    constexpr int NS = kCoopStages;             // register stages of the loaders
+    constexpr int NS = coop_stages(D, DV);  // register stages of the loaders
     constexpr int VPL = kChunk * 4 / NL;        // V pieces per loader thread per chunk
     constexpr int VRS = NL / 4;                 // rows between two V pieces of one loader thread
     constexpr int SL = DV / 32;    // column slices (workgroups) per sequence segment
@@ -233,10 +237,8 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     const int qk_loff = qk_row * RSQ + qk_cc * 8;
     const int v_loff = v_row * RSV + v_cc * 8, vs_loff = v_row * RSVS + v_cc * 8;
 
-    // Two register stages: chunk c travels in stage c & 1 from the moment its loads are issued
-    // (two chunks ahead of the iteration that writes it to LDS) until it is written.  (A third
-    // stage measured no faster: the loaders are bound by the rate at which one compute unit
-    // can pull data through its vector memory path, not by latency.)
+    // NS register stages: chunk c travels in stage c % NS from the moment its loads are issued
+    // (NS chunks ahead of the iteration that writes it to LDS) until it is written.
     struct Stage {
         u32x4 k[QPL], v[VPL];
     };
