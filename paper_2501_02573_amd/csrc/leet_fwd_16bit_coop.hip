@@ -131,11 +131,11 @@ __device__ __forceinline__ f32x16 zero16() {
 // Two loader waves (four measured no faster) with two or three register stages each.  Over inputs that
 // come from memory the loads are bound by what a compute unit keeps in flight, so a third stage pays
 // where it costs nothing else: at D = 64, whose chunks are half the bytes (B8 H16 N4000 70.8 -> 67.7 us with
-// fp32 and 62.9 -> 61.4 with fp16 outputs, B1 H16 N16000 59.9 -> 55.8), and a little at value width 256
-// (B1 H32 N2000 40.6 -> 40.2).  D = DV = 128 keeps two: its row waves fill the registers (B2 H16 N2048 29.1
-// against 29.7, B1 H32 N777 13.9 against 14.1).  Four spill at D = 128 and gain nothing more at 64.
+// fp32 and 63.5 -> 60.1 with fp16 outputs, B1 H16 N16000 59.9 -> 55.8).  D = 128 keeps two: its row waves
+// fill the registers (B2 H16 N2048 29.1 against 29.7, B1 H32 N777 13.9 against 14.1; width 256, N2000 32.3
+// against 32.4).  Four spill at D = 128 and gain nothing more at 64.
 constexpr int kCoopLoaderWaves = 2;
-constexpr int coop_stages(int D, int DV) { return D == 64 || DV == 256 ? 3 : 2; }
+constexpr int coop_stages(int D) { return D == 64 ? 3 : 2; }
 constexpr int kCoopThreads = 384 + 64 * kCoopLoaderWaves;
 
 // D: width of q and k rows (rank); DV: width of v and out rows (DV / 32 slices per sequence).
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     auto mfma32 = [](u32x4 a, u32x4 b, f32x16 c) { return E::mfma32(a, b, c); };
     constexpr int NT = kCoopThreads;            // two row waves, two state waves, two store waves and the loader waves
     constexpr int NL = 64 * kCoopLoaderWaves;   // loader threads (waves 6 and up)
-    constexpr int NS = coop_stages(D, DV);  // register stages of the loaders
+    constexpr int NS = coop_stages(D);  // register stages of the loaders
     constexpr int VPL = kChunk * 4 / NL;        // V pieces per loader thread per chunk
     constexpr int VRS = NL / 4;                 // rows between two V pieces of one loader thread
     constexpr int SL = DV / 32;    // column slices (workgroups) per sequence segment
