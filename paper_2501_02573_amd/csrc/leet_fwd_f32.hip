@@ -8,14 +8,14 @@
 //     S_{t+1} = gamma^L S_t + (Gam K_t)^T V_t                Lam = diag(gamma^(i+1)), Gam = diag(gamma^(L-1-j))
 //
 // The fp32 matrix instructions run at a sixteenth of the bf16 rate, and a kernel built on them is
-// bound by their issue.  Here every fp32 operand x is written as x0 + x1 + x2 with bf16 terms: x0 is
-// x cut to its upper 16 bits (or the nearest bf16), x1 the rest rounded to bf16, x2 what is left.  8 + 8 + 8 significant
-// bits hold all 24 of x, and bf16 has the exponent range of fp32, so the sum is exactly x (down to
-// 2^-110 in magnitude, where the last terms underflow).  A product needs the six partial products
-// a0 b0, a0 b1, a1 b0, a1 b1, a0 b2, a2 b0; the three left out are below 2^-22 of it in the worst
-// case and about 2^-26 with a random sign on average.  Each partial product is exact in fp32 and the
-// sums are fp32 accumulators as before, with fewer roundings (one instruction contracts 16 or 32
-// terms, not 4): six instructions at 16 times the rate.
+// bound by their issue.  Here every fp32 operand x is written as x0 + x1 + x2 with bf16 terms, each the
+// upper 16 bits of what the terms before it leave: 8 + 8 + 8 significant bits hold all 24 of x, and bf16
+// has the exponent range of fp32, so the sum is exactly x (down to 2^-102 in magnitude, where the last
+// terms are denormal and the matrix instructions take them as zero).  A product needs all partial products
+// but a2 b2, which is below 2^-32 of it: left out, a1 b2 and a2 b1 make one product in itself (a token's first
+// P V, one-hot q and k) wrong by up to 2^-22.  Each partial product is exact in fp32 and the sums are
+// fp32 accumulators as before, with fewer roundings (one instruction contracts 16 or 32 terms, not 4):
+// eight instructions at 16 times the rate.
 // An infinity (x - x0 is then NaN) turns to NaN in the outputs that it reaches.
 //
 // Work split: a column tile of 32 value columns belongs to two waves (in the pre-pass at D = 128: one),
@@ -23,15 +23,15 @@
 // Each computes its half of the sum Q S and the scores' product with one half of the keys; the two sums
 // meet in LDS on their way out.  D = 128: eight waves, one workgroup a compute unit; D = 64: four waves, two.
 //
-// What bounds it: with the matrix units busy the device clocks down (1.6 GHz in a steady run at the
-// headline shape), so work counts more than waiting: per 32-token tile 468 MFMAs of 32 cycles and, per
-// wave, some 700 vector operations, most of them splits.  B4 H16 N4096 d128: 300 -> 219..232 us a call
-// (walk 215 -> 148..164, pre-pass 73 -> 58; the fp32-MFMA kernel issued at 105 TFLOP/s of a 153 TFLOP/s
-// library rate); B2 H8 N2048 d64: 31.2 -> 27; B1 H1 N256 d64: 19.0 -> 14.8; B1 H300 N2000 d128: 815 -> 509.
-// Four waves of 64-register state slices, two workgroups a compute unit and twice the segments: within
-// 3 % at the headline shape, and slower where workgroups are few (B2 H8 N2048 d64: 32).
-// Against 64 bits the error of the outputs halves (2-norm over forty sizes: 1.5e-7..3.2e-7 with fp32 MFMAs,
-// 0.6e-7..1.5e-7 here), that of the states is 0.4 to 0.9 of what it was.
+// What bounds it: matrix and vector instructions, which take turns on a SIMD more than they overlap: per
+// 32-token tile 624 MFMAs of 32 cycles (of 4 SIMDs) and, per wave, some 600 vector operations, most of them
+// splits.  B4 H16 N4096 d128: 255 us a call (303 with fp32 MFMAs, 234 with six partial products); B2 H8 N2048
+// d64: 26.3 (31.1, 26.3); B1 H1 N256 d64: 12.8 (with six 12.9).
+// Four waves of 64-register state slices, two workgroups a compute unit and twice the segments (with six
+// partial products): 215-222 us against 219-232 at the headline shape, but 32 against 26 at B2 H8 N2048 d64.
+// Against 64 bits a single product errs by at most 5.99e-8 of itself (5.95e-8 with fp32 MFMAs; 2.3e-7 with
+// six partial products), and outputs and states that are sums by less than with fp32 MFMAs, whose sums round more
+// often (2-norm over forty sizes, six partial products: outputs 0.6e-7..1.5e-7 against 1.5e-7..3.2e-7).
 //
 // MFMA conventions: an A (B) operand of 32x32x16 (16x16x32) holds, in lane l, row (column) l%32
 // (l%16) and eight contraction slots of group l/32 (l/16); a 32x32 (16x16) accumulator holds column
@@ -91,55 +91,41 @@ struct Frag3 {
     u32x4 x[3];
 };
 
-// Two values -> their three terms, each packed in a pair.  kNear: x0 is the nearest bf16 instead of the upper
-// half, for the operands of the state update.  The terms that follow are then half as large and the left-out
-// products a fourth; a state after two tokens, all of whose error they are otherwise, needs that to be as exact
-// as fp32 products (4.0e-8 against 3.1e-8 without).  The clamp keeps what would round to infinity finite.
+// Two values -> their three terms, each packed in a pair.
 struct Pair3 {
     uint32_t x[3];
 };
-template <bool kNear>
 __device__ __forceinline__ Pair3 split2(float a, float b) {
 #pragma clang fp contract(off)
-    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+    auto upper = [](float lo, float hi) { return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u); };
+    auto rest = [](float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
     Pair3 s;
-    float ra, rb;
-    if (kNear) {
-        const float top = __uint_as_float(0x7f7f0000u);  // largest bf16
-        s.x[0] = ElemBf16::pack2(__builtin_amdgcn_fmed3f(a, -top, top), __builtin_amdgcn_fmed3f(b, -top, top));
-        asm("" : "+v"(s.x[0]));
-        ra = a - ElemBf16::lo(s.x[0]);
-        rb = b - ElemBf16::hi(s.x[0]);
-    } else {
-        s.x[0] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);  // upper halves
-        ra = a - __uint_as_float(ua & 0xffff0000u);
-        rb = b - __uint_as_float(ub & 0xffff0000u);
-    }
-    s.x[1] = ElemBf16::pack2(ra, rb);
-    asm("" : "+v"(s.x[1]));  // one conversion of the pair: the compiler would convert a third time to unpack it
-    s.x[2] = ElemBf16::pack2(ra - ElemBf16::lo(s.x[1]), rb - ElemBf16::hi(s.x[1]));
+    s.x[0] = upper(a, b);
+    const float ra = rest(a), rb = rest(b);
+    s.x[1] = upper(ra, rb);
+    s.x[2] = upper(rest(ra), rest(rb));
     return s;
 }
 
 // words 2e and 2e+1 of an operand
-template <bool kNear>
 __device__ __forceinline__ void put2(Frag3& f, int e, float a, float b) {
-    const Pair3 s = split2<kNear>(a, b);
+    const Pair3 s = split2(a, b);
 #pragma unroll
     for (int i = 0; i < 3; ++i) f.x[i][e] = s.x[i];
 }
 
 // four consecutive values -> 8 bytes of each of the three planes (plane stride `plane` elements)
-template <bool kNear>
 __device__ __forceinline__ void store4(uint16_t* dst, int plane, float a, float b, float c, float d) {
-    const Pair3 lo = split2<kNear>(a, b), hi = split2<kNear>(c, d);
+    const Pair3 lo = split2(a, b), hi = split2(c, d);
 #pragma unroll
     for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x2*>(dst + i * plane) = u32x2{lo.x[i], hi.x[i]};
 }
 
-// The five partial products below the leading one; they have an accumulator of their own, so that
-// their roundings are 2^-8 of the sum's and only the leading product and one addition round at full size.
+// The seven partial products below the leading one; they have an accumulator of their own, so that
+// their roundings are 2^-6 of the sum's and only the leading product and one addition round at full size.
 __device__ __forceinline__ f32x16 mma32_small(const Frag3& a, const Frag3& b, f32x16 c) {
+    c = ElemBf16::mfma32(a.x[1], b.x[2], c);
+    c = ElemBf16::mfma32(a.x[2], b.x[1], c);
     c = ElemBf16::mfma32(a.x[2], b.x[0], c);
     c = ElemBf16::mfma32(a.x[0], b.x[2], c);
     c = ElemBf16::mfma32(a.x[1], b.x[1], c);
@@ -152,6 +138,8 @@ __device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
 }
 
 __device__ __forceinline__ f32x4 mma16_small(const Frag3& a, const Frag3& b, f32x4 c) {
+    c = mfma16(a.x[1], b.x[2], c);
+    c = mfma16(a.x[2], b.x[1], c);
     c = mfma16(a.x[2], b.x[0], c);
     c = mfma16(a.x[0], b.x[2], c);
     c = mfma16(a.x[1], b.x[1], c);
@@ -368,8 +356,8 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
         }
 #pragma unroll
         for (int r = 0; r < NLOAD; ++r) {
-            store4<true>(kt + st_off + RPP * r * RS, kTile * RS, rk[r][0], rk[r][1], rk[r][2], rk[r][3]);
-            if (kOut) store4<false>(sm.q + st_off + RPP * r * RS, kTile * RS, rq[r][0], rq[r][1], rq[r][2], rq[r][3]);
+            store4(kt + st_off + RPP * r * RS, kTile * RS, rk[r][0], rk[r][1], rk[r][2], rk[r][3]);
+            if (kOut) store4(sm.q + st_off + RPP * r * RS, kTile * RS, rq[r][0], rq[r][1], rq[r][2], rq[r][3]);
         }
         __syncthreads();
         // The next tile's loads, in flight during the MFMA work below; the last tile loads itself again.  (Under
@@ -406,7 +394,7 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
                     const bool below = n == 1 || l16 >= q4 + 4 * r;  // on or below the diagonal
                     m[r] = below ? (big[r] + small[r]) * wgt[n / NW][r] : 0.0f;
                 }
-                store4<false>(sm.p + (16 * it + l16) * RP + 16 * jt + 4 * q4, kTile * RP, m[0], m[1], m[2], m[3]);
+                store4(sm.p + (16 * it + l16) * RP + 16 * jt + 4 * q4, kTile * RP, m[0], m[1], m[2], m[3]);
             }
 
             __builtin_amdgcn_sched_barrier(0);
@@ -419,7 +407,7 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
                 for (int i = 0; i < 3; ++i)
                     a.x[i] = *reinterpret_cast<const u32x4*>(&sm.q[i * kTile * RS + q_row32 + 16 * s]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) put2<false>(b, e, S[s >> 1][8 * (s & 1) + 2 * e], S[s >> 1][8 * (s & 1) + 2 * e + 1]);
+                for (int e = 0; e < 4; ++e) put2(b, e, S[s >> 1][8 * (s & 1) + 2 * e], S[s >> 1][8 * (s & 1) + 2 * e + 1]);
             };
             Frag3 a[2], b[2];
             read(a[0], b[0], 0);
@@ -431,9 +419,9 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
                 o = ElemBf16::mfma32(a[s & 1].x[0], b[s & 1].x[0], o);
                 __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  // LDS reads, then MFMAs and vector operations in turn
 #pragma unroll
-                for (int i = 0; i < 6; ++i) {
+                for (int i = 0; i < 8; ++i) {
                     __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x2, 6, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -464,7 +452,7 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
                 for (int i = 0; i < 3; ++i)
                     a.x[i] = *reinterpret_cast<const u32x4*>(&sm.p[i * kTile * RP + ln * RP + 16 * f + 8 * g]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) put2<false>(b, e, va[8 * f + 2 * e], va[8 * f + 2 * e + 1]);
+                for (int e = 0; e < 4; ++e) put2(b, e, va[8 * f + 2 * e], va[8 * f + 2 * e + 1]);
                 os = mma32_small(a, b, os);
                 o = ElemBf16::mfma32(a.x[0], b.x[0], o);
                 put_rows(f == 1 ? 8 : 0, 16);
@@ -484,7 +472,7 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                put2<true>(gv[f], e, va[8 * f + 2 * e] * wv[e >> 1][2 * (e & 1)], va[8 * f + 2 * e + 1] * wv[e >> 1][2 * (e & 1) + 1]);
+                put2(gv[f], e, va[8 * f + 2 * e] * wv[e >> 1][2 * (e & 1)], va[8 * f + 2 * e + 1] * wv[e >> 1][2 * (e & 1) + 1]);
         }
         __builtin_amdgcn_sched_barrier(0);
         load_v(next);
