@@ -51,7 +51,8 @@ extern "C" {
 #endif
 
 typedef enum {
-    LEET_F32 = 0,  /* q, k, v are IEEE binary32; fp32 products as bf16 MFMA sums    */
+    LEET_F32 = 0,  /* q, k, v are IEEE binary32; products on fp32 MFMA (d = 64) or of
+                      three bf16 terms an operand on bf16 MFMA (d = 128)            */
     LEET_BF16 = 1, /* q, k, v are bfloat16; products on bf16 MFMA, fp32 accumulate  */
     LEET_F16 = 2   /* q, k, v are IEEE binary16; products on fp16 MFMA, fp32 accumulate
                       (accepted by the _v2, _rd and _recurrent entry points)       */

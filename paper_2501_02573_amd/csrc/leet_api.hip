@@ -17,8 +17,10 @@ hipError_t launch_fwd_16bit_walk(const FwdParams& p, int BH, int D, int DV, bool
 hipError_t launch_state_pass(const float* state_in, float* state_out, int BH, int D, int DV, hipStream_t stream);
 hipError_t launch_fwd_16bit_coop_states(const FwdParams& p, int BH, int D, int DV, bool f16, hipStream_t stream);
 hipError_t launch_fwd_16bit_coop_walk(const FwdParams& p, int BH, int D, int DV, bool f16, bool out16, hipStream_t stream);
-hipError_t launch_fwd_f32_states(const FwdParams& p, int BH, int D, hipStream_t stream);
-hipError_t launch_fwd_f32_walk(const FwdParams& p, int BH, int D, hipStream_t stream);
+hipError_t launch_fwd_f32_states(const FwdParams& p, int BH, hipStream_t stream);
+hipError_t launch_fwd_f32_walk(const FwdParams& p, int BH, hipStream_t stream);
+hipError_t launch_fwd_f32_split_states(const FwdParams& p, int BH, hipStream_t stream);
+hipError_t launch_fwd_f32_split_walk(const FwdParams& p, int BH, hipStream_t stream);
 hipError_t launch_seg_scan(float* seg_state, const float* state_in, float* state_copy, const float* gamma, int BH, int H,
                            int nseg, int seg_tokens, int step, int D, int DV, hipStream_t stream);
 hipError_t launch_recurrent(const void* q, const void* k, const void* v, const float* gamma, float* out,
@@ -72,7 +74,7 @@ struct Plan {
 // fp32: a walk workgroup that enters segment s after s pre-pass states can read and combine those
 // states itself, which saves the scan kernel's launch and its pass over all states.  It pays while a
 // workgroup has at most this much to read: 3 states at d = 128 (B1 H32 N256: 26.2 -> 23.4 us; 7 states,
-// B1 H32 N512: 31.5 -> 36.3), 15 at d = 64 (3 states: 14.1 -> 12.7, 15 states, B2 H8 N2048: 27.4 -> 26.3).
+// B1 H32 N512: 31.5 -> 36.3), 15 at d = 64 (3 states, B1 H1 N256: 13.9 -> 12.6, 15 states, B2 H8 N2048: 30.9 -> 29.5).
 constexpr size_t kFoldBytes = (size_t)240 << 10;
 
 // The pre-pass is a pure read stream and runs faster with two workgroups per compute unit
@@ -452,10 +454,14 @@ int forward_impl(const void* q, const void* k, const void* v, const float* gamma
     const bool out16 = out_dtype != LEET_F32;
 
     const bool coop = plan.coop;
+    // fp32: products of bf16 terms at width 128, fp32 matrix instructions at width 64, each where it is
+    // the faster (measured beside the kernels)
+    const bool split = d == 128;
     auto launch_states = [&]() {
         return coop   ? leet::launch_fwd_16bit_coop_states(pre, (int)BH, d, dv, f16, s)
                : in16 ? leet::launch_fwd_16bit_states(pre, (int)BH, d, dv, f16, s)
-                      : leet::launch_fwd_f32_states(pre, (int)BH, d, s);
+               : split ? leet::launch_fwd_f32_split_states(pre, (int)BH, s)
+                       : leet::launch_fwd_f32_states(pre, (int)BH, s);
     };
     auto launch_scan = [&]() {
         if (plan.fold) return hipSuccess;
@@ -465,7 +471,8 @@ int forward_impl(const void* q, const void* k, const void* v, const float* gamma
     auto launch_walk = [&]() {
         return coop   ? leet::launch_fwd_16bit_coop_walk(p, (int)BH, d, dv, f16, out16, s)
                : in16 ? leet::launch_fwd_16bit_walk(p, (int)BH, d, dv, f16, out16, s)
-                      : leet::launch_fwd_f32_walk(p, (int)BH, d, s);
+               : split ? leet::launch_fwd_f32_split_walk(p, (int)BH, s)
+                       : leet::launch_fwd_f32_walk(p, (int)BH, s);
     };
 
     if (!kernel_ms) {

@@ -1,208 +1,74 @@
-// Chunk-walk kernel for fp32 inputs (gfx950): fp32 products on the bf16 matrix instructions.
+// Chunk-walk kernel for fp32 inputs of width 64 (gfx950, v_mfma_f32_16x16x4_f32: true fp32 products).
 //
 // Same algorithm as the wide 16-bit kernel: one workgroup per segment of a (batch, head) sequence
-// walks the tokens in order (Alg. 2, Appendix B.2, with the decaying mask of Eq. "BCMV" and the
-// weight split of Alg. 4, Appendix B.3), here in tiles of L = 32 tokens:
+// walks 64-token chunks (Alg. 2, Appendix B.2, with the decaying mask of Eq. "BCMV" and the
+// weight split of Alg. 4, Appendix B.3):
 //
 //     O_t     = ((Q_t K_t^T) .* D) V_t + Lam (Q_t S_t)       D[i][j] = gamma^(i-j), i >= j
 //     S_{t+1} = gamma^L S_t + (Gam K_t)^T V_t                Lam = diag(gamma^(i+1)), Gam = diag(gamma^(L-1-j))
 //
-// The fp32 matrix instructions run at a sixteenth of the bf16 rate, and a kernel built on them is
-// bound by their issue.  Here every fp32 operand x is written as x0 + x1 + x2 with bf16 terms, each the
-// upper 16 bits of what the terms before it leave: 8 + 8 + 8 significant bits hold all 24 of x, and bf16
-// has the exponent range of fp32, so the sum is exactly x (down to 2^-102 in magnitude, where the last
-// terms are denormal and the matrix instructions take them as zero).  A product needs all partial products
-// but a2 b2, which is below 2^-32 of it: left out, a1 b2 and a2 b1 make one product in itself (a token's first
-// P V, one-hot q and k) wrong by up to 2^-22.  Each partial product is exact in fp32 and the sums are
-// fp32 accumulators as before, with fewer roundings (one instruction contracts 16 or 32 terms, not 4):
-// eight instructions at 16 times the rate.
-// An infinity (x - x0 is then NaN) turns to NaN in the outputs that it reaches.
+// fp32 MFMA is 16 times slower than bf16 MFMA, so this kernel is bound by MFMA issue and
+// latency, not by HBM; the work is therefore cut finer than in the 16-bit kernels: wave w owns
+// 16 value columns [16w, 16w+16) of O and of the state S (d/16 waves per workgroup), and all
+// products are 16x16x4 tiles.  At width 128 products of bf16 terms (leet_fwd_f32_split.hip) are faster;
+// here they are not once their operands' range is watched (us a call, B*H x N, here against there: 1 x 256 12.7
+// against 14.3, 16 x 2048 29.6 against 30.2, 128 x 8192 416 against 448; 512 x 512 73.5 against 66.3).
 //
-// Work split: a column tile of 32 value columns belongs to two waves (in the pre-pass at D = 128: one),
-// which hold half of the key dimension each: S[half of dk][cols] in fp32 accumulators for the whole walk.
-// Each computes its half of the sum Q S and the scores' product with one half of the keys; the two sums
-// meet in LDS on their way out.  D = 128: eight waves, one workgroup a compute unit; D = 64: four waves, two.
+// MFMA conventions (16x16x4 fp32): an A (B) operand is one float per lane: lane l holds row
+// (column) l%16 and contraction slot q = l/16; an accumulator holds, in lane l, column l%16
+// and, in register r, row 4q + r.  A contraction may assign indices to slots in any way, as
+// long as A and B agree.  Everything is computed transposed (lane = token), so that an
+// accumulator register of one product is directly an operand of the next:
+//   G1  P^T[j][i]  = sum_dk K[j][dk] Q[i][dk]        A, B: 16-byte LDS reads, 4 MFMAs each
+//       P^T       *= D^T                             per-lane weights, fixed for the kernel
+//   G3  O^T[c][i]  = sum_dk S^T[c][dk] Q^T[dk][i]    A = S accumulator registers, B = Q rows
+//       O^T       *= gamma^(i+1)                     one scalar per lane, since lane = token
+//   G2  O^T[c][i] += sum_j V^T[c][j] P^T[j][i]       A = V[j][c] for j = 16jt + 4q + r, B = P^T registers
+//   G4  S[dk][c]  += sum_j K^T[dk][j] (Gam V)[j][c]  A = K[j][dk], B = the V registers of G2 times Gam
+// The 64 x 64 score matrix has ten non-zero 16 x 16 tiles; each is computed once per workgroup
+// (tile n by wave n mod #waves), masked, and handed to the other waves through LDS in
+// operand-register order.
 //
-// What bounds it: matrix and vector instructions, which take turns on a SIMD more than they overlap: per
-// 32-token tile 624 MFMAs of 32 cycles (of 4 SIMDs) and, per wave, some 600 vector operations, most of them
-// splits.  B4 H16 N4096 d128: 255 us a call (303 with fp32 MFMAs, 234 with six partial products); B2 H8 N2048
-// d64: 26.3 (31.1, 26.3); B1 H1 N256 d64: 12.8 (with six 12.9).
-// Four waves of 64-register state slices, two workgroups a compute unit and twice the segments (with six
-// partial products): 215-222 us against 219-232 at the headline shape, but 32 against 26 at B2 H8 N2048 d64.
-// Against 64 bits a single product errs by at most 5.99e-8 of itself (5.95e-8 with fp32 MFMAs; 2.3e-7 with
-// six partial products), and outputs and states that are sums by less than with fp32 MFMAs, whose sums round more
-// often (2-norm over forty sizes, six partial products: outputs 0.6e-7..1.5e-7 against 1.5e-7..3.2e-7).
-//
-// MFMA conventions: an A (B) operand of 32x32x16 (16x16x32) holds, in lane l, row (column) l%32
-// (l%16) and eight contraction slots of group l/32 (l/16); a 32x32 (16x16) accumulator holds column
-// l%32 (l%16) and, in register r, row 8(r/4) + 4(l/32) + r%4 (row 4(l/16) + r).  A contraction may
-// assign indices to slots in any way, as long as A and B agree.
-//
-//   G1  P^T[j][i]  = sum_dk K[j][dk] Q[i][dk]     three 16x16 tiles (it >= jt), tile n by wave n mod #waves;
-//                                                 accumulator row 4q + r of a tile is key j = 16jt + q + 4r
-//       P^T       *= D^T                          then split and handed to all waves as P[i][slot],
-//                                                 slot 16jt + 4q + r
-//   G3  O[i][c]    = sum_dk Q[i][dk] S[dk][c]     A = Q rows, B = S accumulators, split in registers
-//       O         *= gamma^(i+1)
-//   G2  O[i][c]   += sum_j P[i][j] V[j][c]        A = P rows, B = V, straight from global memory into
-//                                                 registers in slot order (a wave's columns are its own)
-//   G4  S[dk][c]  += sum_j K^T[dk][j] (Gam V)[j][c]   A = K through transposing LDS reads
-//                                                 (ds_read_b64_tr_b16), B = the V registers times Gam
-// Slots of 16 keys run 0 4 8 12, 1 5 9 13, ...: a transposing read then touches rows four apart,
-// which the padded rows spread over all LDS banks.  G4 assigns key-dimension index dk = 32t + pi(m)
-// to accumulator row m (pi swaps bits 2 and 3), so that registers 8h..8h+7 of S hold the eight
-// consecutive dk that one 16-byte Q read contracts with.
-// O accumulators are columns across lanes: a store instruction writes two whole 128-byte row pieces.
-//
-// A ragged last tile (L < 32) is left-aligned and zero below its tokens: all weights stay valid but
-// Gam = gamma^(L-1-j), and gamma^L.
+// A ragged last chunk (L < 64) is right-aligned in the tile: rows 64-L.. hold the tokens,
+// rows above are zero, so the intra-chunk weights (functions of i-j and of 63-j) stay valid;
+// only Lam and gamma^L depend on L.
 #include "leet_common.hpp"
 
 namespace leet {
 
-namespace f32k {
+constexpr int kF32Dim = 64;
 
-constexpr int kTile = 32;  // tokens per step of the walk
-
-// The waves of a column tile: two share the key dimension, except in the pre-pass at D = 128.
-constexpr int parts(int D, bool out) { return out || D == 64 ? 2 : 1; }
-constexpr int threads(int D, bool out) { return D / 32 * parts(D, out) * 64; }
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-
-// The pre-pass (kOut = false) reads no Q and forms no scores; it has two K buffers instead and so
-// one barrier a tile.
-template <int D, bool kOut>
-struct Smem {
-    static constexpr int RS = D + 8;    // padded row strides (elements)
-    static constexpr int RP = kTile + 8;
-    static constexpr int RO = kTile + 8;  // output scratch of a wave (floats)
-    uint16_t k[kOut ? 1 : 2][3 * kTile * RS];   // three planes each
-    uint16_t q[kOut ? 3 * kTile * RS : 8];
-    uint16_t p[kOut ? 3 * kTile * RP : 8];      // masked scores P[i][slot]
-    float o[kOut ? 2 * (D / 32) * kTile * RO : 4];  // output tiles of the waves
-    float lw[kTile];       // gamma^(i+1)
-    float gw[kTile];       // gamma^(31-j) in slot order
-    float pw[kTile + 4];   // gamma^n, n = 0..32
+// The pre-pass (kOut = false) reads no Q and forms no scores, and its workgroups need less LDS.
+template <bool kOut>
+struct F32Smem {
+    static constexpr int D = kF32Dim, RS = D + 4;  // padded row stride (floats)
+    float q[kOut ? kChunk * RS : 4];
+    float k[kChunk * RS];
+    float v[kChunk * RS];
+    f32x4 pfrag[kOut ? 10 : 1][64];   // masked P^T tiles: [tile][lane], registers 0..3
+    float pw[kChunk + 4];             // gamma^n, n = 0..64
 };
 
-// an operand as three bf16 terms
-struct Frag3 {
-    u32x4 x[3];
-};
-
-// Two values -> their three terms, each packed in a pair.
-struct Pair3 {
-    uint32_t x[3];
-};
-__device__ __forceinline__ Pair3 split2(float a, float b) {
-#pragma clang fp contract(off)
-    auto upper = [](float lo, float hi) { return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u); };
-    auto rest = [](float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
-    Pair3 s;
-    s.x[0] = upper(a, b);
-    const float ra = rest(a), rb = rest(b);
-    s.x[1] = upper(ra, rb);
-    s.x[2] = upper(rest(ra), rest(rb));
-    return s;
-}
-
-// words 2e and 2e+1 of an operand
-__device__ __forceinline__ void put2(Frag3& f, int e, float a, float b) {
-    const Pair3 s = split2(a, b);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) f.x[i][e] = s.x[i];
-}
-
-// four consecutive values -> 8 bytes of each of the three planes (plane stride `plane` elements)
-__device__ __forceinline__ void store4(uint16_t* dst, int plane, float a, float b, float c, float d) {
-    const Pair3 lo = split2(a, b), hi = split2(c, d);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x2*>(dst + i * plane) = u32x2{lo.x[i], hi.x[i]};
-}
-
-// The seven partial products below the leading one; they have an accumulator of their own, so that
-// their roundings are 2^-6 of the sum's and only the leading product and one addition round at full size.
-__device__ __forceinline__ f32x16 mma32_small(const Frag3& a, const Frag3& b, f32x16 c) {
-    c = ElemBf16::mfma32(a.x[1], b.x[2], c);
-    c = ElemBf16::mfma32(a.x[2], b.x[1], c);
-    c = ElemBf16::mfma32(a.x[2], b.x[0], c);
-    c = ElemBf16::mfma32(a.x[0], b.x[2], c);
-    c = ElemBf16::mfma32(a.x[1], b.x[1], c);
-    c = ElemBf16::mfma32(a.x[1], b.x[0], c);
-    return ElemBf16::mfma32(a.x[0], b.x[1], c);
-}
-
-__device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-__device__ __forceinline__ f32x4 mma16_small(const Frag3& a, const Frag3& b, f32x4 c) {
-    c = mfma16(a.x[1], b.x[2], c);
-    c = mfma16(a.x[2], b.x[1], c);
-    c = mfma16(a.x[2], b.x[0], c);
-    c = mfma16(a.x[0], b.x[2], c);
-    c = mfma16(a.x[1], b.x[1], c);
-    c = mfma16(a.x[1], b.x[0], c);
-    return mfma16(a.x[0], b.x[1], c);
-}
-
-// ds_read_b64_tr_b16: within each group of 16 lanes, lane i receives element i%4 of
-// the 8-byte rows addressed by lanes i/4, 4+i/4, 8+i/4, 12+i/4 of the group.
-__device__ __forceinline__ u32x2 lds_tr(const uint16_t* p) {
-    s16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) s16x4*)(const_cast<uint16_t*>(p)));
-    return __builtin_bit_cast(u32x2, r);
-}
-
-// The tile of tokens tok0 .. min(tok0 + 31, tok_end - 1) of a tensor with rows of D floats.
-template <int D>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const float* base, int tok0, int tok_end) {
-    // all of it is the same in every lane; the compiler is told, since it moves part of the arithmetic to vector registers
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(base) + (size_t)tok0 * (D * 4);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)addr), hi = __builtin_amdgcn_readfirstlane((uint32_t)(addr >> 32));
-    const int bytes = __builtin_amdgcn_readfirstlane(min(kTile, tok_end - tok0) * (D * 4));
-    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uintptr_t)hi << 32) | lo), 0, bytes, 0x00027000);
-}
-// kStream: with the nontemporal hint
-template <bool kStream>
-__device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, int off) {
-    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kStream ? 2 : 0));
-}
-__device__ __forceinline__ float load1(__amdgpu_buffer_rsrc_t r, int off) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
-// nontemporal: the output is written once and not read again here
-__device__ __forceinline__ void store4_nt(f32x4 x, __amdgpu_buffer_rsrc_t r, int off) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), r, off, 0, 2);
-}
-
-}  // namespace f32k
+// The ten score tiles (it >= jt) in production order.
+__device__ __forceinline__ constexpr int f32_tile_it(int n) { return n < 1 ? 0 : n < 3 ? 1 : n < 6 ? 2 : 3; }
+__device__ __forceinline__ constexpr int f32_tile_jt(int n) { return n - (f32_tile_it(n) * (f32_tile_it(n) + 1)) / 2; }
 
 // kOut = true : full walk (outputs + state).   kOut = false : state only (segment pre-pass).
-// kStream: q, k, v exceed the last-level cache; q and k, read in whole lines, are loaded nontemporally (not v,
-// whose lines two instructions share).  B4 H16 N4096 d128: 234 -> 230 us.
-template <int D, bool kOut, bool kStream>
-__global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdParams p) {
-    using namespace f32k;
-    constexpr int CT = D / 32;                 // column tiles
-    constexpr int KS = parts(D, kOut);         // waves of a column tile: parts of the key dimension
-    constexpr int NW = CT * KS;                // waves
-    constexpr int NT = NW * 64;                // threads
-    constexpr int DT = D / 32 / KS;            // 32-row tiles of the state that a wave holds
-    using Sm = Smem<D, kOut>;
-    constexpr int RS = Sm::RS, RP = Sm::RP, RO = Sm::RO;
+template <bool kOut>
+__global__ __launch_bounds__(kF32Dim * 4, 2) void fwd_f32_kernel(FwdParams p) {
+    constexpr int D = kF32Dim;
+    constexpr int NT = D * 4;                  // threads: one wave per 16 value columns
+    constexpr int NW = D / 16;                 // waves
+    constexpr int DT = D / 16;                 // 16-row tiles of the key dimension
+    constexpr int RS = F32Smem<kOut>::RS;
     constexpr int PR = D / 4;                  // 16-byte pieces per row
-    constexpr int NLOAD = kTile * PR / NT;     // pieces per thread of q and of k
-    constexpr int RPP = NT / PR;               // rows one pass of all threads covers
-    constexpr int NSLOT = (3 + NW - 1) / NW;   // score tiles per wave, at most
-    __shared__ __attribute__((aligned(16))) Sm sm;
+    constexpr int NLOAD = kChunk * PR / NT;    // pieces per thread per tensor (= 4)
+    constexpr int ROWS_PER_PASS = NT / PR;     // rows one pass of all threads covers (= 16)
+    constexpr int NSLOT = (10 + NW - 1) / NW;  // score tiles per wave, at most
+    __shared__ __attribute__((aligned(16))) F32Smem<kOut> sm;
 
     const int tid = threadIdx.x;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l = tid & 63, ln = l & 31, g = l >> 5, l16 = l & 15, q4 = l >> 4;
-    const int half = (l >> 4) & 1;
-    const int wc = w % CT, wk = w / CT;  // column tile, part of the key dimension
+    const int w = tid >> 6, l = tid & 63, ln = l & 15, qd = l >> 4;
     const int nseg_launch = kOut ? p.nseg : p.nseg - 1;
     const int bh = blockIdx.x / nseg_launch;
     const int seg = blockIdx.x % nseg_launch;
@@ -210,7 +76,7 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
 
     const int tok_begin = seg * p.seg_chunks * kChunk;
     const int tok_end = (seg == p.nseg - 1) ? p.N : tok_begin + p.seg_chunks * kChunk;
-    const int ntiles = (tok_end - tok_begin + kTile - 1) / kTile;
+    const int nchunks = (tok_end - tok_begin + kChunk - 1) / kChunk;
 
     const size_t seq_off = (size_t)bh * p.N * D;
     const float* qb = reinterpret_cast<const float*>(p.q) + seq_off;
@@ -218,68 +84,28 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
     const float* vb = reinterpret_cast<const float*>(p.v) + seq_off;
     float* ob = static_cast<float*>(p.out) + seq_off;
 
-    // ---- global memory.  Every tile is addressed through buffer descriptors of its L D floats: what lies
-    // beyond a ragged tile reads as zero and is not written, with no branch and no clamped address.
-    // q, k: piece r of this thread is row RPP r + tid/PR, floats 4(tid%PR)..+3; v: this lane's column, the
-    // sixteen keys of its slots; out: row 8m + l/8, floats 32w + 4(l%8)..+3.
-    const int j0 = tid / PR, cc = tid % PR;
-    const int c_own = 32 * wc + ln;
-    f32x4 rq[NLOAD], rk[NLOAD];
-    float va[16];  // va[8f + e] = V[key_of(f, e)][c_own]
-    auto key_of = [&](int f, int e) { return 16 * f + 2 * g + (e >> 2) + 4 * (e & 3); };
-    const int qk_off = (j0 * D + cc * 4) * 4, v_off = (2 * g * D + c_own) * 4, o_off = ((16 * wk + (l >> 3)) * D + 32 * wc + 4 * (l & 7)) * 4;
-    auto load_qk = [&](int tok0) {
-        const auto kt = tile_rsrc<D>(kb, tok0, tok_end);
-        const auto qt = tile_rsrc<D>(qb, tok0, tok_end);
-#pragma unroll
-        for (int r = 0; r < NLOAD; ++r) {
-            rk[r] = load4<kStream>(kt, qk_off + RPP * r * D * 4);
-            if (kOut) rq[r] = load4<kStream>(qt, qk_off + RPP * r * D * 4);
-        }
-    };
-    auto load_v = [&](int tok0) {
-        const auto vt = tile_rsrc<D>(vb, tok0, tok_end);
-#pragma unroll
-        for (int x = 0; x < 16; ++x) va[x] = load1(vt, v_off + (16 * (x >> 3) + ((x >> 2) & 1) + 4 * (x & 3)) * D * 4);
-    };
-    load_qk(tok_begin);
-    load_v(tok_begin);
-
     {
         const double gd = p.no_decay ? 1.0 : (double)p.gamma[h];
-        for (int n = tid; n <= kTile; n += NT) {
-            const float x = (float)pow_int(gd, n);
-            sm.pw[n] = x;
-            if (n > 0) sm.lw[n - 1] = x;
-            if (n < kTile) {
-                const int j = kTile - 1 - n;  // slot 16(j/16) + 4(j%4) + (j/4)%4
-                sm.gw[(j & 16) + 4 * (j & 3) + ((j >> 2) & 3)] = x;
-            }
-        }
+        for (int n = tid; n <= kChunk; n += NT) sm.pw[n] = (float)pow_int(gd, n);
     }
 
-    // state slice: S[t][r] = S[dk = 32t + pi(m(r, g))][c_own]
-    f32x16 S[DT];
-    auto dk_of = [&](int t, int r) {
-        // m = 8(r/4) + 4g + r%4 ; pi swaps the 4- and 8-bits: dk = 16(r/8) + 8g + 4((r/4)&1) + r%4
-        return 32 * (DT * wk + t) + 16 * (r >> 3) + 8 * g + 4 * ((r >> 2) & 1) + (r & 3);
-    };
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) S[t][r] = 0.0f;
-    auto load_state = [&](const float* src, f32x16 (&x)[DT]) {
+    // state slice: S[t][r] = S[dk = 16t + 4q + r][c = 16w + ln]
+    f32x4 S[DT];
+    const int c_own = 16 * w + ln;
+    auto load_state = [&](const float* src, f32x4 (&x)[DT]) {
 #pragma unroll
         for (int t = 0; t < DT; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) x[t][r] = src[dk_of(t, r) * D + c_own];
+            for (int r = 0; r < 4; ++r) x[t][r] = src[(16 * t + 4 * qd + r) * D + c_own];
     };
     auto store_state = [&](float* dst) {
 #pragma unroll
         for (int t = 0; t < DT; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) dst[dk_of(t, r) * D + c_own] = S[t][r];
+            for (int r = 0; r < 4; ++r) dst[(16 * t + 4 * qd + r) * D + c_own] = S[t][r];
     };
+#pragma unroll
+    for (int t = 0; t < DT; ++t) S[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (kOut) {
         const float* slots = p.seg_state + (size_t)bh * p.state_slots * D * D;
         if (seg == 0) {
@@ -293,12 +119,12 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
             load_state(slots, S);
 #pragma unroll 1
             for (int j = 1; j < seg; ++j) {
-                f32x16 a[DT];
+                f32x4 a[DT];
                 load_state(slots + (size_t)j * D * D, a);
 #pragma unroll
                 for (int t = 0; t < DT; ++t)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) S[t][r] = gl * S[t][r] + a[t][r];
+                    for (int r = 0; r < 4; ++r) S[t][r] = gl * S[t][r] + a[t][r];
             }
         }
     } else if (p.fold && seg == 0 && p.state_in) {
@@ -306,217 +132,135 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
         store_state(p.state_copy + (size_t)bh * D * D);
     }
 
-    __syncthreads();  // tables visible
+    __syncthreads();  // table visible
 
-    // decay weights of the score tiles this wave produces: tile n = (it, jt) = (0,0), (1,0), (1,1);
-    // register r of a lane is query 16 it + l16, key 16 jt + q4 + 4 r
-    f32x4 wgt[NSLOT];
-    if (kOut) {
+    // per-lane constants of the walk
+    f32x4 wgt[NSLOT];   // decay weights of the score tiles this wave produces
+    float gam[16];      // gamma^(63-j) for the keys j = 16jt + 4q + r this lane feeds to G2 and G4
 #pragma unroll
-        for (int n = 0; n < 3; ++n) {
-            if (n % NW != w) continue;
+    for (int n = 0; n < 10; ++n) {
+        if (n % NW != w) continue;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int d = (n == 1 ? 16 : 0) + l16 - (q4 + 4 * r);  // i - j
-                wgt[n / NW][r] = d >= 0 ? sm.pw[max(d, 0)] : 0.0f;
-            }
+        for (int r = 0; r < 4; ++r) {
+            const int d = 16 * (f32_tile_it(n) - f32_tile_jt(n)) + ln - (4 * qd + r);  // i - j
+            wgt[n / NW][r] = (d >= 0) ? sm.pw[max(d, 0)] : 0.0f;
         }
     }
-
-    // per-lane LDS offsets (elements)
-    const int st_off = j0 * RS + cc * 4;                       // staging: + RPP r RS
-    const int q_row32 = ln * RS + 32 * DT * wk + 8 * g;                       // G3: + 32 t + 16 h
-    const int q_row16 = l16 * RS + 8 * q4;                     // G1: + 16 it RS + 32 s
-    const int k_row16 = ((l16 >> 2) + 4 * (l16 & 3)) * RS + 8 * q4;  // G1: + 16 jt RS + 32 s
-    const int k_tr = (2 * g + 4 * (l16 >> 2)) * RS + 32 * DT * wk + 16 * half + 8 * (l16 & 1) + 4 * ((l16 >> 1) & 1);  // G4: + 16 f RS + 32 t, + RS
-
-    // The finished tile of tokens tok0 ..: the two waves of a column tile hold half of the sum each; each adds
-    // and stores half of the rows, in whole 128-byte row pieces, all LDS reads before the first store.
-    auto store_out = [&](int tok0) {
-        f32x4 val[2];
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            const float* src = sm.o + wc * (kTile * RO) + (16 * wk + 8 * m + (l >> 3)) * RO + 4 * (l & 7);
-            val[m] = *reinterpret_cast<const f32x4*>(src) + *reinterpret_cast<const f32x4*>(src + CT * kTile * RO);
-        }
-        const auto ot = tile_rsrc<D>(ob, tok0, tok_end);
-#pragma unroll
-        for (int m = 0; m < 2; ++m) store4_nt(val[m], ot, o_off + 8 * m * D * 4);
-    };
+    for (int e = 0; e < 16; ++e) gam[e] = sm.pw[kChunk - 1 - (16 * (e >> 2) + 4 * qd + (e & 3))];
 
-    for (int t = 0; t < ntiles; ++t) {
-        const int tok0 = tok_begin + t * kTile;
-        const int next = tok_begin + min(t + 1, ntiles - 1) * kTile;
-        const int Lc = min(kTile, tok_end - tok0);
-        uint16_t* kt = sm.k[kOut ? 0 : (t & 1)];
-
-        if (kOut && t > 0) {
-            __syncthreads();  // the previous tile's sums visible; everyone is done reading its planes and scores
-            store_out(tok0 - kTile);
-        }
+    // staging: piece r of this thread is row ROWS_PER_PASS*r + tid/PR, floats 4(tid%PR)..+3
+    const int j0 = tid / PR, cc = tid % PR;
+    f32x4 rq[NLOAD], rk[NLOAD], rv[NLOAD];
+    auto prefetch = [&](int tok0) {
+        const int shift = max(0, tok0 + kChunk - tok_end);  // rows [0, shift) of the tile stay zero
 #pragma unroll
         for (int r = 0; r < NLOAD; ++r) {
-            store4(kt + st_off + RPP * r * RS, kTile * RS, rk[r][0], rk[r][1], rk[r][2], rk[r][3]);
-            if (kOut) store4(sm.q + st_off + RPP * r * RS, kTile * RS, rq[r][0], rq[r][1], rq[r][2], rq[r][3]);
+            const int j = ROWS_PER_PASS * r + j0;
+            const bool ok = j >= shift;
+            const size_t off = (size_t)(tok0 - shift + j) * D + cc * 4;
+            const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+            if (kOut) rq[r] = ok ? *reinterpret_cast<const f32x4*>(qb + off) : z;
+            rk[r] = ok ? *reinterpret_cast<const f32x4*>(kb + off) : z;
+            rv[r] = ok ? *reinterpret_cast<const f32x4*>(vb + off) : z;
+        }
+    };
+
+    prefetch(tok_begin);
+
+    for (int t = 0; t < nchunks; ++t) {
+        const int tok0 = tok_begin + t * kChunk;
+        const int Lc = min(kChunk, tok_end - tok0);
+        const int shift = kChunk - Lc;
+
+        if (t > 0) __syncthreads();  // everyone is done reading the previous chunk's tiles and P fragments
+#pragma unroll
+        for (int r = 0; r < NLOAD; ++r) {
+            const int j = ROWS_PER_PASS * r + j0;
+            if (kOut) *reinterpret_cast<f32x4*>(&sm.q[j * RS + cc * 4]) = rq[r];
+            *reinterpret_cast<f32x4*>(&sm.k[j * RS + cc * 4]) = rk[r];
+            *reinterpret_cast<f32x4*>(&sm.v[j * RS + cc * 4]) = rv[r];
         }
         __syncthreads();
-        // The next tile's loads, in flight during the MFMA work below; the last tile loads itself again.  (Under
-        // a condition, every later wait would have to cover the path without them and so drain them.)
-        load_qk(next);
-        __builtin_amdgcn_sched_barrier(0);
+        if (t + 1 < nchunks) prefetch(tok0 + kChunk);  // in flight during the MFMA work below
 
-        f32x16 o, os;  // leading products, the others
+        f32x4 o[4];
         if (kOut) {
             // G1 + mask for the score tiles this wave produces
 #pragma unroll
-            for (int n = 0; n < 3; ++n) {
+            for (int n = 0; n < 10; ++n) {
                 if (n % NW != w) continue;
-                const int it = n > 0, jt = n > 1;
-                f32x4 big = {0.f, 0.f, 0.f, 0.f}, small = {0.f, 0.f, 0.f, 0.f};
-                auto read = [&](Frag3& a, Frag3& b, int s) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                const float* krow = &sm.k[(16 * f32_tile_jt(n) + ln) * RS + 4 * qd];
+                const float* qrow = &sm.q[(16 * f32_tile_it(n) + ln) * RS + 4 * qd];
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        a.x[i] = *reinterpret_cast<const u32x4*>(&kt[i * kTile * RS + k_row16 + 16 * jt * RS + 32 * s]);
-                        b.x[i] = *reinterpret_cast<const u32x4*>(&sm.q[i * kTile * RS + q_row16 + 16 * it * RS + 32 * s]);
-                    }
-                };
-                Frag3 a[2], b[2];
-                read(a[0], b[0], 0);
+                for (int s = 0; s < D / 16; ++s) {
+                    const f32x4 a = *reinterpret_cast<const f32x4*>(krow + 16 * s);
+                    const f32x4 b = *reinterpret_cast<const f32x4*>(qrow + 16 * s);
 #pragma unroll
-                for (int s = 0; s < D / 32; ++s) {
-                    if (s + 1 < D / 32) read(a[(s + 1) & 1], b[(s + 1) & 1], s + 1);
-                    small = mma16_small(a[s & 1], b[s & 1], small);
-                    big = mfma16(a[s & 1].x[0], b[s & 1].x[0], big);
+                    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
                 }
-                float m[4];
+                if (f32_tile_it(n) == f32_tile_jt(n)) {  // above the diagonal: zero whatever the product is
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const bool below = n == 1 || l16 >= q4 + 4 * r;  // on or below the diagonal
-                    m[r] = below ? (big[r] + small[r]) * wgt[n / NW][r] : 0.0f;
+                    for (int r = 0; r < 4; ++r) acc[r] = ln >= 4 * qd + r ? acc[r] : 0.0f;
                 }
-                store4(sm.p + (16 * it + l16) * RP + 16 * jt + 4 * q4, kTile * RP, m[0], m[1], m[2], m[3]);
+                sm.pfrag[n][l] = acc * wgt[n / NW];
             }
 
-            __builtin_amdgcn_sched_barrier(0);
-            // G3: O = Q S, rows of O scaled by gamma^(i+1).  The operands of step s + 1 are read and split
-            // between the MFMAs of step s.
+            // G3: O^T = S^T Q^T, rows of O scaled by gamma^(i+1)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) o[r] = os[r] = 0.0f;
-            auto read = [&](Frag3& a, Frag3& b, int s) {
+            for (int it = 0; it < 4; ++it) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                const float* qrow = &sm.q[(16 * it + ln) * RS + 4 * qd];
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    a.x[i] = *reinterpret_cast<const u32x4*>(&sm.q[i * kTile * RS + q_row32 + 16 * s]);
+                for (int dt = 0; dt < DT; ++dt) {
+                    const f32x4 b = *reinterpret_cast<const f32x4*>(qrow + 16 * dt);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) put2(b, e, S[s >> 1][8 * (s & 1) + 2 * e], S[s >> 1][8 * (s & 1) + 2 * e + 1]);
-            };
-            Frag3 a[2], b[2];
-            read(a[0], b[0], 0);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int s = 0; s < 2 * DT; ++s) {
-                if (s + 1 < 2 * DT) read(a[(s + 1) & 1], b[(s + 1) & 1], s + 1);
-                os = mma32_small(a[s & 1], b[s & 1], os);
-                o = ElemBf16::mfma32(a[s & 1].x[0], b[s & 1].x[0], o);
-                __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  // LDS reads, then MFMAs and vector operations in turn
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x2, 6, 0);
+                    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(S[dt][e], b[e], acc, 0, 0, 0);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const f32x4 lam = *reinterpret_cast<const f32x4*>(&sm.lw[8 * u + 4 * g]);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    o[4 * u + r] *= lam[r];
-                    os[4 * u + r] *= lam[r];
-                }
-            }
-
-            __syncthreads();  // scores visible
-            // G2: O += P V.  Keys 16..31 do not reach rows 0..15 (registers 0..7), which are done before them.
-            // Wave part 0 takes keys 0..15, part 1 keys 16..31; both leave their sums for store_out.
-            float* mine = sm.o + w * (kTile * RO);
-            auto put_rows = [&](int r0, int r1) {
-#pragma unroll
-                for (int r = r0; r < r1; ++r) mine[(8 * (r >> 2) + 4 * g + (r & 3)) * RO + ln] = o[r] + os[r];
-            };
-#pragma unroll
-            for (int f = 0; f < 2; ++f) {
-                if (f != wk) continue;
-                if (f == 1) put_rows(0, 8);
-                Frag3 a, b;
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    a.x[i] = *reinterpret_cast<const u32x4*>(&sm.p[i * kTile * RP + ln * RP + 16 * f + 8 * g]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) put2(b, e, va[8 * f + 2 * e], va[8 * f + 2 * e + 1]);
-                os = mma32_small(a, b, os);
-                o = ElemBf16::mfma32(a.x[0], b.x[0], o);
-                put_rows(f == 1 ? 8 : 0, 16);
+                o[it] = acc * sm.pw[max(16 * it + ln + 1 - shift, 0)];
             }
         }
 
-        // Gam V as operands; with them the registers of V are free for the next tile's loads.
-        Frag3 gv[2];
+        // V registers: va[4jt + r] = V[j = 16jt + 4q + r][c_own]
+        float va[16];
 #pragma unroll
-        for (int f = 0; f < 2; ++f) {
-            f32x4 wv[2];
+        for (int e = 0; e < 16; ++e) va[e] = sm.v[(16 * (e >> 2) + 4 * qd + (e & 3)) * RS + c_own];
+
+        if (kOut) {
+            __syncthreads();  // P fragments visible
+            // G2: O^T += V^T P^T over the tiles (jt <= it)
 #pragma unroll
-            for (int u = 0; u < 2; ++u) wv[u] = *reinterpret_cast<const f32x4*>(&sm.gw[16 * f + 8 * g + 4 * u]);
-            if (Lc < kTile) {  // ragged: gamma^(L-1-j)
+            for (int n = 0; n < 10; ++n) {
+                const f32x4 pt = sm.pfrag[n][l];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) wv[e >> 2][e & 3] = sm.pw[max(Lc - 1 - key_of(f, e), 0)];
+                for (int r = 0; r < 4; ++r)
+                    o[f32_tile_it(n)] = __builtin_amdgcn_mfma_f32_16x16x4f32(va[4 * f32_tile_jt(n) + r], pt[r],
+                                                                            o[f32_tile_it(n)], 0, 0, 0);
             }
+            // store O^T: lane = token 16it + ln, registers = columns 16w + 4q + (0..3)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                put2(gv[f], e, va[8 * f + 2 * e] * wv[e >> 1][2 * (e & 1)], va[8 * f + 2 * e + 1] * wv[e >> 1][2 * (e & 1) + 1]);
+            for (int it = 0; it < 4; ++it) {
+                const int i = 16 * it + ln;
+                if (i >= shift)  // written once, not read again here: nontemporal
+                    __builtin_nontemporal_store(o[it], reinterpret_cast<f32x4*>(ob + (size_t)(tok0 - shift + i) * D + 16 * w + 4 * qd));
+            }
         }
-        __builtin_amdgcn_sched_barrier(0);
-        load_v(next);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_sched_barrier(0);
-        // G4: S = gamma^L S + K^T (Gam V)
+
+        // G4: S = gamma^L S + K^T (Gam V); contraction slot q of step (jt, r) is key 16jt + 4q + r
         {
             const float gl = sm.pw[Lc];
-            auto read = [&](Frag3& a, int u) {  // step u: tile u/2, slots 16 (u%2) ..
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const uint16_t* src = &kt[i * kTile * RS + k_tr + 16 * (u & 1) * RS + 32 * (u >> 1)];
-                    const u32x2 lo = lds_tr(src), hi = lds_tr(src + RS);
-                    a.x[i] = u32x4{lo.x, lo.y, hi.x, hi.y};
-                }
-            };
-            Frag3 a[4];
-            read(a[0], 0);
-            read(a[1], 1);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int dt = 0; dt < DT; ++dt) S[dt] *= gl;
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                const int c = 2 * (dt & 1);
-                if (dt + 1 < DT) {
-                    read(a[c ^ 2], 2 * dt + 2);
-                    read(a[(c ^ 2) + 1], 2 * dt + 3);
-                }
-                f32x16 sb, ss;  // leading products, the others
+            for (int e = 0; e < 16; ++e) {
+                const float b = va[e] * gam[e];
+                const float* krow = &sm.k[(16 * (e >> 2) + 4 * qd + (e & 3)) * RS + ln];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) sb[r] = ss[r] = 0.0f;
-                ss = mma32_small(a[c], gv[0], ss);
-                ss = mma32_small(a[c + 1], gv[1], ss);
-                sb = ElemBf16::mfma32(a[c].x[0], gv[0].x[0], sb);
-                sb = ElemBf16::mfma32(a[c + 1].x[0], gv[1].x[0], sb);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) S[dt][r] = __builtin_fmaf(S[dt][r], gl, sb[r] + ss[r]);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int dt = 0; dt < DT; ++dt)
+                    S[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(krow[16 * dt], b, S[dt], 0, 0, 0);
             }
         }
-    }
-
-    if (kOut) {
-        __syncthreads();  // the last tile's sums visible
-        store_out(tok_begin + (ntiles - 1) * kTile);
     }
 
     float* dst = nullptr;
@@ -528,25 +272,14 @@ __global__ __launch_bounds__(f32k::threads(D, kOut), 2) void fwd_f32_kernel(FwdP
     if (dst) store_state(dst);
 }
 
-namespace {
-template <int D, bool kOut>
-void launch_f32(const FwdParams& p, int blocks, hipStream_t stream) {
-    const dim3 grid(blocks), block(f32k::threads(D, kOut));
-    if (p.stream_loads) hipLaunchKernelGGL((fwd_f32_kernel<D, kOut, true>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((fwd_f32_kernel<D, kOut, false>), grid, block, 0, stream, p);
-}
-}  // namespace
-
-hipError_t launch_fwd_f32_states(const FwdParams& p, int BH, int D, hipStream_t stream) {
+hipError_t launch_fwd_f32_states(const FwdParams& p, int BH, hipStream_t stream) {
     if (p.nseg <= 1) return hipSuccess;
-    if (D == 64) launch_f32<64, false>(p, BH * (p.nseg - 1), stream);
-    else launch_f32<128, false>(p, BH * (p.nseg - 1), stream);
+    hipLaunchKernelGGL((fwd_f32_kernel<false>), dim3(BH * (p.nseg - 1)), dim3(4 * kF32Dim), 0, stream, p);
     return hipGetLastError();
 }
 
-hipError_t launch_fwd_f32_walk(const FwdParams& p, int BH, int D, hipStream_t stream) {
-    if (D == 64) launch_f32<64, true>(p, BH * p.nseg, stream);
-    else launch_f32<128, true>(p, BH * p.nseg, stream);
+hipError_t launch_fwd_f32_walk(const FwdParams& p, int BH, hipStream_t stream) {
+    hipLaunchKernelGGL((fwd_f32_kernel<true>), dim3(BH * p.nseg), dim3(4 * kF32Dim), 0, stream, p);
     return hipGetLastError();
 }
 
