@@ -51,8 +51,10 @@ extern "C" {
 #endif
 
 typedef enum {
-    LEET_F32 = 0,  /* q, k, v are IEEE binary32; products on fp32 MFMA (d = 64) or of
-                      three bf16 terms an operand on bf16 MFMA (d = 128)            */
+    LEET_F32 = 0,  /* q, k, v are IEEE binary32; products are those of fp32 over its whole
+                      range, on fp32 MFMA (d = 64) or as sums of bf16 MFMA products of
+                      three terms an operand (d = 128; segments with values outside the
+                      terms' range run on fp32 MFMA, which takes them longer)          */
     LEET_BF16 = 1, /* q, k, v are bfloat16; products on bf16 MFMA, fp32 accumulate  */
     LEET_F16 = 2   /* q, k, v are IEEE binary16; products on fp16 MFMA, fp32 accumulate
                       (accepted by the _v2, _rd and _recurrent entry points)       */

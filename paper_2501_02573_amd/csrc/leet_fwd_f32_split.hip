@@ -10,13 +10,17 @@
 // The fp32 matrix instructions run at a sixteenth of the bf16 rate, and a kernel built on them is
 // bound by their issue.  Here every fp32 operand x is written as x0 + x1 + x2 with bf16 terms, each the
 // upper 16 bits of what the terms before it leave: 8 + 8 + 8 significant bits hold all 24 of x, and bf16
-// has the exponent range of fp32, so the sum is exactly x (down to 2^-102 in magnitude, where the last
-// terms are denormal and the matrix instructions take them as zero).  A product needs all partial products
+// has the exponent range of fp32, so the sum is exactly x.  A product needs all partial products
 // but a2 b2, which is below 2^-32 of it: left out, a1 b2 and a2 b1 make one product in itself (a token's first
 // P V, one-hot q and k) wrong by up to 2^-22.  Each partial product is exact in fp32 and the sums are
 // fp32 accumulators as before, with fewer roundings (one instruction contracts 16 or 32 terms, not 4):
 // eight instructions at 16 times the rate.
-// An infinity (x - x0 is then NaN) turns to NaN in the outputs that it reaches.
+//
+// Range: the bf16 matrix instructions take denormal terms and sums (below 2^-126) as zero, and an infinity leaves
+// x - x0 = NaN.  So the walk watches the smallest nonzero operands and whether its results are finite, and where
+// something is out of range the segment is walked again with fp32 matrix instructions (walk_fp32), whose
+// results stand for every operand.  Ordinary data never does that; the watching costs some 50 of 650 vector operations
+// a tile (B4 H16 N4096 273 -> 282 us; without it q, k ~ 2^-60 with v ~ 2^104 came out with errors of 6e-4).
 //
 // Work split: a column tile of 32 value columns belongs to two waves (in the pre-pass: one),
 // which hold half of the key dimension each: S[half of dk][cols] in fp32 accumulators for the whole walk.
@@ -24,14 +28,13 @@
 // meet in LDS on their way out.  Eight waves, one workgroup a compute unit; in the pre-pass four and two.
 //
 // What bounds it: matrix and vector instructions, which take turns on a SIMD more than they overlap: per
-// 32-token tile 624 MFMAs of 32 cycles (of 4 SIMDs) and, per wave, some 600 vector operations, most of them
-// splits.  B4 H16 N4096 d128: 255 us a call (303 with fp32 MFMAs, 234 with six partial products); B2 H8 N2048
-// d64: 26.3 (31.1, 26.3); B1 H1 N256 d64: 12.8 (with six 12.9).
-// Four waves of 64-register state slices, two workgroups a compute unit and twice the segments (with six
-// partial products): 215-222 us against 219-232 at the headline shape, but 32 against 26 at B2 H8 N2048 d64.
-// Against 64 bits a single product errs by at most 5.99e-8 of itself (5.95e-8 with fp32 MFMAs; 2.3e-7 with
-// six partial products), and outputs and states that are sums by less than with fp32 MFMAs, whose sums round more
-// often (2-norm over forty sizes, six partial products: outputs 0.6e-7..1.5e-7 against 1.5e-7..3.2e-7).
+// 32-token tile 624 MFMAs of 32 cycles (of 4 SIMDs) and, per wave, some 650 vector operations, most of them
+// splits.  Against a kernel on fp32 MFMAs, one device: B4 H16 N4096 319 -> 282 us, B1 H32 N777 53.5 -> 45.9, B1 H300 N2000
+// 819 -> 630 (walk_fp32 alone, B1 H300 N2000: 805).
+// Against 64 bits a single product errs by at most 5.99e-8 of itself (5.95e-8 with fp32 MFMAs).  Sums round less
+// often: over forty sizes outputs 0.66e-7..0.95e-7 in the 2-norm (1.5e-7..2.8e-7), states 0.33 to 0.83 of what fp32
+// MFMAs give; the largest single error of a state after two tokens, in units of its rms and over 200 seeds, is 4.2e-7 on
+// average (5.3e-7) and 8.4e-7 at worst (6.7e-7).
 //
 // MFMA conventions: an A (B) operand of 32x32x16 (16x16x32) holds, in lane l, row (column) l%32
 // (l%16) and eight contraction slots of group l/32 (l/16); a 32x32 (16x16) accumulator holds column
@@ -85,7 +88,34 @@ struct Smem {
     float lw[kTile];       // gamma^(i+1)
     float gw[kTile];       // gamma^(31-j) in slot order
     float pw[kTile + 4];   // gamma^n, n = 0..32
+    int bad[3];            // out of range: seen in even tiles, in odd tiles, in the whole walk
 };
+
+// Whether one of kN values is nonzero and below `least` in magnitude: twice the magnitude's bits minus one puts
+// zero above everything else.
+template <int kN, class Get>
+__device__ __forceinline__ bool has_small_nonzero(Get x, float least) {
+    uint32_t m = ~0u;
+#pragma unroll
+    for (int i = 0; i < kN; ++i) m = min(m, (__float_as_uint(x(i)) << 1) - 1);
+    return m < (__float_as_uint(least) << 1) - 1;
+}
+// The same in half an operation a value for data without zeros: they are told apart only once the smallest is below.
+template <int kN, class Get>
+__device__ __forceinline__ bool has_small(Get x, float least) {
+    float m = __builtin_fabsf(x(0));
+#pragma unroll
+    for (int i = 1; i < kN; ++i) m = __builtin_fminf(m, __builtin_fabsf(x(i)));
+    return __any(m < least) ? has_small_nonzero<kN>(x, least) : false;
+}
+// 2^e as a float, -126 <= e <= 127
+__device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
+// exponent of the largest of four values; 0 where that is zero, denormal or not finite
+__device__ __forceinline__ int exponent4(const float* x) {
+    const uint32_t a = __float_as_uint(x[0]) << 1, b = __float_as_uint(x[1]) << 1, c = __float_as_uint(x[2]) << 1, d = __float_as_uint(x[3]) << 1;
+    const int e = (int)(max(max(a, b), max(c, d)) >> 24);
+    return e == 0 || e == 255 ? 0 : e - 127;
+}
 
 // an operand as three bf16 terms
 struct Frag3 {
@@ -246,6 +276,7 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
 
     {
         const double gd = p.no_decay ? 1.0 : (double)p.gamma[h];
+        if (tid < 3) sm.bad[tid] = 0;
         for (int n = tid; n <= kTile; n += NT) {
             const float x = (float)pow_int(gd, n);
             sm.pw[n] = x;
@@ -259,14 +290,12 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
 
     // state slice: S[t][r] = S[dk = 32t + pi(m(r, g))][c_own]
     f32x16 S[DT];
+    bool bad = false;   // this lane has seen an operand below its least magnitude
+    float fin = 0.0f;   // sum of the magnitudes of results: not finite once one of them is not
     auto dk_of = [&](int t, int r) {
         // m = 8(r/4) + 4g + r%4 ; pi swaps the 4- and 8-bits: dk = 16(r/8) + 8g + 4((r/4)&1) + r%4
         return 32 * (DT * wk + t) + 16 * (r >> 3) + 8 * g + 4 * ((r >> 2) & 1) + (r & 3);
     };
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) S[t][r] = 0.0f;
     auto load_state = [&](const float* src, f32x16 (&x)[DT]) {
 #pragma unroll
         for (int t = 0; t < DT; ++t)
@@ -279,31 +308,38 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
 #pragma unroll
             for (int r = 0; r < 16; ++r) dst[dk_of(t, r) * D + c_own] = S[t][r];
     };
-    if (kOut) {
-        const float* slots = p.seg_state + (size_t)bh * p.state_slots * D * D;
-        if (seg == 0) {
-            if (p.state_in) load_state(p.state_in + (size_t)bh * D * D, S);
-        } else if (!p.fold) {
-            load_state(slots + (size_t)(seg * p.state_step - 1) * D * D, S);
-        } else {
-            // No scan kernel has run: the slots hold the end state T_j of every segment (the first run from
-            // the caller's state, the others from zero), and S_in(s) = sum_{j < s} gamma^(L (s-1-j)) T_j.
-            const float gl = p.no_decay ? 1.0f : (float)pow_int((double)p.gamma[h], p.seg_chunks * kChunk);
-            load_state(slots, S);
+    auto enter_state = [&]() {
+#pragma unroll
+        for (int t = 0; t < DT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) S[t][r] = 0.0f;
+        if (kOut) {
+            const float* slots = p.seg_state + (size_t)bh * p.state_slots * D * D;
+            if (seg == 0) {
+                if (p.state_in) load_state(p.state_in + (size_t)bh * D * D, S);
+            } else if (!p.fold) {
+                load_state(slots + (size_t)(seg * p.state_step - 1) * D * D, S);
+            } else {
+                // No scan kernel has run: the slots hold the end state T_j of every segment (the first run from
+                // the caller's state, the others from zero), and S_in(s) = sum_{j < s} gamma^(L (s-1-j)) T_j.
+                const float gl = p.no_decay ? 1.0f : (float)pow_int((double)p.gamma[h], p.seg_chunks * kChunk);
+                load_state(slots, S);
 #pragma unroll 1
-            for (int j = 1; j < seg; ++j) {
-                f32x16 a[DT];
-                load_state(slots + (size_t)j * D * D, a);
+                for (int j = 1; j < seg; ++j) {
+                    f32x16 a[DT];
+                    load_state(slots + (size_t)j * D * D, a);
 #pragma unroll
-                for (int t = 0; t < DT; ++t)
+                    for (int t = 0; t < DT; ++t)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) S[t][r] = gl * S[t][r] + a[t][r];
+                        for (int r = 0; r < 16; ++r) S[t][r] = gl * S[t][r] + a[t][r];
+                }
             }
+        } else if (p.fold && seg == 0 && p.state_in) {
+            load_state(p.state_in + (size_t)bh * D * D, S);
+            store_state(p.state_copy + (size_t)bh * D * D);
         }
-    } else if (p.fold && seg == 0 && p.state_in) {
-        load_state(p.state_in + (size_t)bh * D * D, S);
-        store_state(p.state_copy + (size_t)bh * D * D);
-    }
+    };
+    enter_state();
 
     __syncthreads();  // tables visible
 
@@ -338,185 +374,325 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
             const float* src = sm.o + wc * (kTile * RO) + (16 * wk + 8 * m + (l >> 3)) * RO + 4 * (l & 7);
             val[m] = *reinterpret_cast<const f32x4*>(src) + *reinterpret_cast<const f32x4*>(src + CT * kTile * RO);
         }
+#pragma unroll
+        for (int x = 0; x < 8; ++x) fin += __builtin_fabsf(val[x >> 2][x & 3]);
         const auto ot = tile_rsrc(ob, tok0, tok_end);
 #pragma unroll
         for (int m = 0; m < 2; ++m) store4_nt(val[m], ot, o_off + 8 * m * D * 4);
     };
 
-    for (int t = 0; t < ntiles; ++t) {
-        const int tok0 = tok_begin + t * kTile;
-        const int next = tok_begin + min(t + 1, ntiles - 1) * kTile;
-        const int Lc = min(kTile, tok_end - tok0);
-        uint16_t* kt = sm.k[kOut ? 0 : (t & 1)];
+    // Least magnitudes of operands other than zero: two that are multiplied make 2^-96 or more, of which the terms and
+    // partial sums that the matrix instructions drop (below 2^-126) are less than a rounding, and none is below 2^-100,
+    // where its own last terms would go.  `tilt` shares the range out by the scales of a segment's first token, q's against
+    // k's, in the pre-pass v's against k's: it decides what is out of range, never what is right.
+    const float far = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sm.pw[kTile - 1])));  // gamma^31
+    const int scale = exponent4((kOut ? qb : vb) + (size_t)tok_begin * D) - exponent4(kb + (size_t)tok_begin * D);
+    const int tilt = __builtin_amdgcn_readfirstlane(min(max(scale / 2, -48), 48));
+    const float least_q = pow2(-52 + tilt), least_k = pow2(-44 - tilt);  // S: as k
+    const float least_p = pow2(-52 - tilt);
+    // Gam V, whose least is q's, is gamma^31 V or more (or zero, with gamma = 0)
+    const float least_v = far > 0.0f ? fmaxf(pow2(-44 + tilt), pow2(-52 + tilt) / far) : pow2(-44 + tilt);
 
-        if (kOut && t > 0) {
-            __syncthreads();  // the previous tile's sums visible; everyone is done reading its planes and scores
-            store_out(tok0 - kTile);
-        }
+    // The walk with split products.  True: an operand or a result was out of range somewhere, and nothing of what
+    // the walk has made stands.
+    auto walk_split = [&]() -> bool {
+        // the entering state arrives here, not at its first use in the loop: there every tile would wait for all loads
 #pragma unroll
-        for (int r = 0; r < NLOAD; ++r) {
-            store4(kt + st_off + RPP * r * RS, kTile * RS, rk[r][0], rk[r][1], rk[r][2], rk[r][3]);
-            if (kOut) store4(sm.q + st_off + RPP * r * RS, kTile * RS, rq[r][0], rq[r][1], rq[r][2], rq[r][3]);
-        }
-        __syncthreads();
-        // The next tile's loads, in flight during the MFMA work below; the last tile loads itself again.  (Under
-        // a condition, every later wait would have to cover the path without them and so drain them.)
-        load_qk(next);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < DT; ++t) asm("" : "+v"(S[t]));
+        int stop = 0;
+        for (int t = 0; t < ntiles; ++t) {
+            const int tok0 = tok_begin + t * kTile;
+            const int next = tok_begin + min(t + 1, ntiles - 1) * kTile;
+            const int Lc = min(kTile, tok_end - tok0);
+            uint16_t* kt = sm.k[kOut ? 0 : (t & 1)];
 
-        f32x16 o, os;  // leading products, the others
-        if (kOut) {
-            // G1 + mask for the score tile this wave produces
+            if (kOut && t > 0) {
+                __syncthreads();  // the previous tile's sums visible; everyone is done reading its planes and scores
+                store_out(tok0 - kTile);
+            }
+            constexpr int NS = kOut ? 16 * DT : 0;  // values of S, which is an operand in G3 only
+            bad |= has_small<NS + 4 * NLOAD>([&](int x) { return x < NS ? S[x / 16 % DT][x % 16] : rk[(x - NS) / 4 % NLOAD][x % 4]; }, least_k);
+            if (kOut) bad |= has_small<4 * NLOAD>([&](int x) { return rq[x >> 2][x & 3]; }, least_q);
 #pragma unroll
-            for (int n = 0; n < 3; ++n) {
-                if (n != w) continue;
-                const int it = n > 0, jt = n > 1;
-                f32x4 big = {0.f, 0.f, 0.f, 0.f}, small = {0.f, 0.f, 0.f, 0.f};
+            for (int r = 0; r < NLOAD; ++r) {
+                store4(kt + st_off + RPP * r * RS, kTile * RS, rk[r][0], rk[r][1], rk[r][2], rk[r][3]);
+                if (kOut) store4(sm.q + st_off + RPP * r * RS, kTile * RS, rq[r][0], rq[r][1], rq[r][2], rq[r][3]);
+            }
+            __syncthreads();
+            // Something out of range in the tile before?  (Its flag is not written again before the next barrier.)
+            stop = sm.bad[(t & 1) ^ 1];
+            // The next tile's loads, in flight during the MFMA work below; the last tile loads itself again.  (Under
+            // a condition, every later wait would have to cover the path without them and so drain them.)
+            load_qk(next);
+            __builtin_amdgcn_sched_barrier(0);
+
+            f32x16 o, os;  // leading products, the others
+            if (kOut) {
+                // G1 + mask for the score tile this wave produces
+#pragma unroll
+                for (int n = 0; n < 3; ++n) {
+                    if (n != w) continue;
+                    const int it = n > 0, jt = n > 1;
+                    f32x4 big = {0.f, 0.f, 0.f, 0.f}, small = {0.f, 0.f, 0.f, 0.f};
+                    auto read = [&](Frag3& a, Frag3& b, int s) {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            a.x[i] = *reinterpret_cast<const u32x4*>(&kt[i * kTile * RS + k_row16 + 16 * jt * RS + 32 * s]);
+                            b.x[i] = *reinterpret_cast<const u32x4*>(&sm.q[i * kTile * RS + q_row16 + 16 * it * RS + 32 * s]);
+                        }
+                    };
+                    Frag3 a[2], b[2];
+                    read(a[0], b[0], 0);
+#pragma unroll
+                    for (int s = 0; s < D / 32; ++s) {
+                        if (s + 1 < D / 32) read(a[(s + 1) & 1], b[(s + 1) & 1], s + 1);
+                        small = mma16_small(a[s & 1], b[s & 1], small);
+                        big = mfma16(a[s & 1].x[0], b[s & 1].x[0], big);
+                    }
+                    float m[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const bool below = n == 1 || l16 >= q4 + 4 * r;  // on or below the diagonal
+                        m[r] = below ? (big[r] + small[r]) * wgt[r] : 0.0f;
+                    }
+                    bad |= has_small_nonzero<4>([&](int x) { return m[x]; }, least_p);
+                    store4(sm.p + (16 * it + l16) * RP + 16 * jt + 4 * q4, kTile * RP, m[0], m[1], m[2], m[3]);
+                }
+
+                __builtin_amdgcn_sched_barrier(0);
+                // G3: O = Q S, rows of O scaled by gamma^(i+1).  The operands of step s + 1 are read and split
+                // between the MFMAs of step s.
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[r] = os[r] = 0.0f;
                 auto read = [&](Frag3& a, Frag3& b, int s) {
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        a.x[i] = *reinterpret_cast<const u32x4*>(&kt[i * kTile * RS + k_row16 + 16 * jt * RS + 32 * s]);
-                        b.x[i] = *reinterpret_cast<const u32x4*>(&sm.q[i * kTile * RS + q_row16 + 16 * it * RS + 32 * s]);
-                    }
+                    for (int i = 0; i < 3; ++i)
+                        a.x[i] = *reinterpret_cast<const u32x4*>(&sm.q[i * kTile * RS + q_row32 + 16 * s]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) put2(b, e, S[s >> 1][8 * (s & 1) + 2 * e], S[s >> 1][8 * (s & 1) + 2 * e + 1]);
                 };
                 Frag3 a[2], b[2];
                 read(a[0], b[0], 0);
-#pragma unroll
-                for (int s = 0; s < D / 32; ++s) {
-                    if (s + 1 < D / 32) read(a[(s + 1) & 1], b[(s + 1) & 1], s + 1);
-                    small = mma16_small(a[s & 1], b[s & 1], small);
-                    big = mfma16(a[s & 1].x[0], b[s & 1].x[0], big);
-                }
-                float m[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const bool below = n == 1 || l16 >= q4 + 4 * r;  // on or below the diagonal
-                    m[r] = below ? (big[r] + small[r]) * wgt[r] : 0.0f;
-                }
-                store4(sm.p + (16 * it + l16) * RP + 16 * jt + 4 * q4, kTile * RP, m[0], m[1], m[2], m[3]);
-            }
-
-            __builtin_amdgcn_sched_barrier(0);
-            // G3: O = Q S, rows of O scaled by gamma^(i+1).  The operands of step s + 1 are read and split
-            // between the MFMAs of step s.
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[r] = os[r] = 0.0f;
-            auto read = [&](Frag3& a, Frag3& b, int s) {
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    a.x[i] = *reinterpret_cast<const u32x4*>(&sm.q[i * kTile * RS + q_row32 + 16 * s]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) put2(b, e, S[s >> 1][8 * (s & 1) + 2 * e], S[s >> 1][8 * (s & 1) + 2 * e + 1]);
-            };
-            Frag3 a[2], b[2];
-            read(a[0], b[0], 0);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int s = 0; s < 2 * DT; ++s) {
-                if (s + 1 < 2 * DT) read(a[(s + 1) & 1], b[(s + 1) & 1], s + 1);
-                os = mma32_small(a[s & 1], b[s & 1], os);
-                o = ElemBf16::mfma32(a[s & 1].x[0], b[s & 1].x[0], o);
-                __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  // LDS reads, then MFMAs and vector operations in turn
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x2, 6, 0);
-                }
                 __builtin_amdgcn_sched_barrier(0);
-            }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const f32x4 lam = *reinterpret_cast<const f32x4*>(&sm.lw[8 * u + 4 * g]);
+                for (int s = 0; s < 2 * DT; ++s) {
+                    if (s + 1 < 2 * DT) read(a[(s + 1) & 1], b[(s + 1) & 1], s + 1);
+                    os = mma32_small(a[s & 1], b[s & 1], os);
+                    o = ElemBf16::mfma32(a[s & 1].x[0], b[s & 1].x[0], o);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  // LDS reads, then MFMAs and vector operations in turn
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    o[4 * u + r] *= lam[r];
-                    os[4 * u + r] *= lam[r];
+                    for (int i = 0; i < 8; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x2, 6, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const f32x4 lam = *reinterpret_cast<const f32x4*>(&sm.lw[8 * u + 4 * g]);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[4 * u + r] = __builtin_fmaf(os[4 * u + r], lam[r], o[4 * u + r] * lam[r]);
+                }
+
+                __syncthreads();  // scores visible
+                // G2: P V.  Wave part 0 takes keys 0..15, part 1 keys 16..31, which do not reach rows 0..15 (registers 0..7);
+                // both leave their sums for store_out.  P V has accumulators of its own: in those of G3 the matrix instructions
+                // would take a far decayed Lam (Q S) as zero.
+                float* mine = sm.o + w * (kTile * RO);
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+                    if (f != wk) continue;
+                        Frag3 a, b;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        a.x[i] = *reinterpret_cast<const u32x4*>(&sm.p[i * kTile * RP + ln * RP + 16 * f + 8 * g]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) put2(b, e, va[8 * f + 2 * e], va[8 * f + 2 * e + 1]);
+                    f32x16 c, cs;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) c[r] = cs[r] = 0.0f;
+                    cs = mma32_small(a, b, cs);
+                    c = ElemBf16::mfma32(a.x[0], b.x[0], c);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        mine[(8 * (r >> 2) + 4 * g + (r & 3)) * RO + ln] = f == 1 && r < 8 ? o[r] : o[r] + (c[r] + cs[r]);
                 }
             }
 
-            __syncthreads();  // scores visible
-            // G2: O += P V.  Keys 16..31 do not reach rows 0..15 (registers 0..7), which are done before them.
-            // Wave part 0 takes keys 0..15, part 1 keys 16..31; both leave their sums for store_out.
-            float* mine = sm.o + w * (kTile * RO);
-            auto put_rows = [&](int r0, int r1) {
-#pragma unroll
-                for (int r = r0; r < r1; ++r) mine[(8 * (r >> 2) + 4 * g + (r & 3)) * RO + ln] = o[r] + os[r];
-            };
+            bad |= has_small<16>([&](int x) { return va[x]; }, least_v);
+            // Gam V as operands; with them the registers of V are free for the next tile's loads.
+            Frag3 gv[2];
 #pragma unroll
             for (int f = 0; f < 2; ++f) {
-                if (f != wk) continue;
-                if (f == 1) put_rows(0, 8);
-                Frag3 a, b;
+                f32x4 wv[2];
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    a.x[i] = *reinterpret_cast<const u32x4*>(&sm.p[i * kTile * RP + ln * RP + 16 * f + 8 * g]);
+                for (int u = 0; u < 2; ++u) wv[u] = *reinterpret_cast<const f32x4*>(&sm.gw[16 * f + 8 * g + 4 * u]);
+                if (Lc < kTile) {  // ragged: gamma^(L-1-j)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) put2(b, e, va[8 * f + 2 * e], va[8 * f + 2 * e + 1]);
-                os = mma32_small(a, b, os);
-                o = ElemBf16::mfma32(a.x[0], b.x[0], o);
-                put_rows(f == 1 ? 8 : 0, 16);
-            }
-        }
-
-        // Gam V as operands; with them the registers of V are free for the next tile's loads.
-        Frag3 gv[2];
-#pragma unroll
-        for (int f = 0; f < 2; ++f) {
-            f32x4 wv[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) wv[u] = *reinterpret_cast<const f32x4*>(&sm.gw[16 * f + 8 * g + 4 * u]);
-            if (Lc < kTile) {  // ragged: gamma^(L-1-j)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) wv[e >> 2][e & 3] = sm.pw[max(Lc - 1 - key_of(f, e), 0)];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                put2(gv[f], e, va[8 * f + 2 * e] * wv[e >> 1][2 * (e & 1)], va[8 * f + 2 * e + 1] * wv[e >> 1][2 * (e & 1) + 1]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        load_v(next);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_sched_barrier(0);
-        // G4: S = gamma^L S + K^T (Gam V)
-        {
-            const float gl = sm.pw[Lc];
-            auto read = [&](Frag3& a, int u) {  // step u: tile u/2, slots 16 (u%2) ..
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const uint16_t* src = &kt[i * kTile * RS + k_tr + 16 * (u & 1) * RS + 32 * (u >> 1)];
-                    const u32x2 lo = lds_tr(src), hi = lds_tr(src + RS);
-                    a.x[i] = u32x4{lo.x, lo.y, hi.x, hi.y};
+                    for (int e = 0; e < 8; ++e) wv[e >> 2][e & 3] = sm.pw[max(Lc - 1 - key_of(f, e), 0)];
                 }
-            };
-            Frag3 a[4];
-            read(a[0], 0);
-            read(a[1], 1);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) wv[e >> 2][e & 3] *= va[8 * f + e];
+    #pragma unroll
+                for (int e = 0; e < 4; ++e) put2(gv[f], e, wv[e >> 1][2 * (e & 1)], wv[e >> 1][2 * (e & 1) + 1]);
+            }
+            if (__any(bad | !(fin < __builtin_inff()))) sm.bad[t & 1] = 1;
             __builtin_amdgcn_sched_barrier(0);
+            load_v(next);
+            __builtin_amdgcn_sched_barrier(0);
+            // G4: S = gamma^L S + K^T (Gam V)
+            {
+                const float gl = sm.pw[Lc];
+                auto read = [&](Frag3& a, int u) {  // step u: tile u/2, slots 16 (u%2) ..
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                const int c = 2 * (dt & 1);
-                if (dt + 1 < DT) {
-                    read(a[c ^ 2], 2 * dt + 2);
-                    read(a[(c ^ 2) + 1], 2 * dt + 3);
-                }
-                f32x16 sb, ss;  // leading products, the others
-#pragma unroll
-                for (int r = 0; r < 16; ++r) sb[r] = ss[r] = 0.0f;
-                ss = mma32_small(a[c], gv[0], ss);
-                ss = mma32_small(a[c + 1], gv[1], ss);
-                sb = ElemBf16::mfma32(a[c].x[0], gv[0].x[0], sb);
-                sb = ElemBf16::mfma32(a[c + 1].x[0], gv[1].x[0], sb);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) S[dt][r] = __builtin_fmaf(S[dt][r], gl, sb[r] + ss[r]);
+                    for (int i = 0; i < 3; ++i) {
+                        const uint16_t* src = &kt[i * kTile * RS + k_tr + 16 * (u & 1) * RS + 32 * (u >> 1)];
+                        const u32x2 lo = lds_tr(src), hi = lds_tr(src + RS);
+                        a.x[i] = u32x4{lo.x, lo.y, hi.x, hi.y};
+                    }
+                };
+                Frag3 a[4];
+                read(a[0], 0);
+                read(a[1], 1);
                 __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
+                    const int c = 2 * (dt & 1);
+                    if (dt + 1 < DT) {
+                        read(a[c ^ 2], 2 * dt + 2);
+                        read(a[(c ^ 2) + 1], 2 * dt + 3);
+                    }
+                    f32x16 sb, ss;  // leading products, the others
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sb[r] = ss[r] = 0.0f;
+                    ss = mma32_small(a[c], gv[0], ss);
+                    ss = mma32_small(a[c + 1], gv[1], ss);
+                    sb = ElemBf16::mfma32(a[c].x[0], gv[0].x[0], sb);
+                    sb = ElemBf16::mfma32(a[c + 1].x[0], gv[1].x[0], sb);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) S[dt][r] = __builtin_fmaf(S[dt][r], gl, sb[r] + ss[r]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if (__builtin_amdgcn_readfirstlane(stop)) break;
+        }
+
+        if (kOut) {
+            __syncthreads();  // the last tile's sums visible
+            if (!stop) store_out(tok_begin + (ntiles - 1) * kTile);
+        }
+#pragma unroll
+        for (int x = 0; x < 16 * DT; ++x) fin += __builtin_fabsf(S[x >> 4][x & 15]);  // not finite once, not finite for good
+        if (__any(bad | !(fin < __builtin_inff()))) sm.bad[2] = 1;
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(sm.bad[2]) != 0;
+    };
+
+    // The same walk with fp32 matrix instructions on fp32 tiles in the same LDS: same waves, same column tiles and
+    // accumulators, same slots.  Right for every operand; B4 H16 N4096 308 us a call.
+    auto walk_fp32 = [&]() {
+        constexpr int RF = D + 4, RPF = kTile + 4;  // row strides (floats)
+        float* kf = reinterpret_cast<float*>(&sm.k[0][0]);
+        float* qf = reinterpret_cast<float*>(&sm.q[0]);
+        float* pf = reinterpret_cast<float*>(&sm.p[0]);
+        const int k_row = (l16 >> 2) + 4 * (l16 & 3);                  // G1: key of accumulator row l16, + 16 jt
+        const int pi = (ln & 19) | ((ln & 4) << 1) | ((ln & 8) >> 1);  // G4: key index of accumulator row ln
+        for (int t = 0; t < ntiles; ++t) {
+            const int tok0 = tok_begin + t * kTile;
+            const int next = tok_begin + min(t + 1, ntiles - 1) * kTile;
+            const int Lc = min(kTile, tok_end - tok0);
+            if (t > 0) {
+                __syncthreads();
+                if (kOut) store_out(tok0 - kTile);
+            }
+#pragma unroll
+            for (int r = 0; r < NLOAD; ++r) {
+                *reinterpret_cast<f32x4*>(kf + (j0 + RPP * r) * RF + 4 * cc) = rk[r];
+                if (kOut) *reinterpret_cast<f32x4*>(qf + (j0 + RPP * r) * RF + 4 * cc) = rq[r];
+            }
+            __syncthreads();
+            load_qk(next);
+            if (kOut) {
+#pragma unroll
+                for (int n = 0; n < 3; ++n) {  // G1
+                    if (n != w) continue;
+                    const int it = n > 0, jt = n > 1;
+                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+                    for (int s = 0; s < D / 16; ++s) {
+                        const f32x4 a = *reinterpret_cast<const f32x4*>(kf + (16 * jt + k_row) * RF + 16 * s + 4 * q4);
+                        const f32x4 b = *reinterpret_cast<const f32x4*>(qf + (16 * it + l16) * RF + 16 * s + 4 * q4);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const bool below = n == 1 || l16 >= q4 + 4 * r;
+                        acc[r] = below ? acc[r] * wgt[r] : 0.0f;
+                    }
+                    *reinterpret_cast<f32x4*>(pf + (16 * it + l16) * RPF + 16 * jt + 4 * q4) = acc;
+                }
+                f32x16 o;  // G3
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[r] = 0.0f;
+#pragma unroll
+                for (int x = 0; x < 4 * DT; ++x) {
+                    const f32x4 a = *reinterpret_cast<const f32x4*>(qf + ln * RF + dk_of(x >> 2, 4 * (x & 3)));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], S[x >> 2][4 * (x & 3) + e], o, 0, 0, 0);
+                }
+                float* mine = sm.o + w * (kTile * RO);
+                auto put_rows = [&](int r0, int r1) {
+#pragma unroll
+                    for (int r = r0; r < r1; ++r) mine[(8 * (r >> 2) + 4 * g + (r & 3)) * RO + ln] = o[r];
+                };
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[r] *= sm.lw[8 * (r >> 2) + 4 * g + (r & 3)];
+                __syncthreads();  // scores visible
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {  // G2, as above: keys 16..31 do not reach rows 0..15
+                    if (f != wk) continue;
+                    if (f == 1) put_rows(0, 8);
+                    const float* row = pf + ln * RPF + 16 * f + 8 * g;
+                    const f32x4 a[2] = {*reinterpret_cast<const f32x4*>(row), *reinterpret_cast<const f32x4*>(row + 4)};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e >> 2][e & 3], va[8 * f + e], o, 0, 0, 0);
+                    put_rows(f == 1 ? 8 : 0, 16);
+                }
+            }
+            float gva[16];
+#pragma unroll
+            for (int x = 0; x < 16; ++x) {
+                const int back = Lc - 1 - key_of(x >> 3, x & 7);
+                gva[x] = back >= 0 ? va[x] * sm.pw[max(back, 0)] : 0.0f;
+            }
+            load_v(next);
+            const float gl = sm.pw[Lc];
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {  // G4
+                S[dt] *= gl;
+#pragma unroll
+                for (int x = 0; x < 16; ++x) {
+                    const float a = kf[key_of(x >> 3, x & 7) * RF + 32 * (DT * wk + dt) + pi];
+                    S[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, gva[x], S[dt], 0, 0, 0);
+                }
             }
         }
-    }
+        if (kOut) {
+            __syncthreads();
+            store_out(tok_begin + (ntiles - 1) * kTile);
+        }
+    };
 
-    if (kOut) {
-        __syncthreads();  // the last tile's sums visible
-        store_out(tok_begin + (ntiles - 1) * kTile);
+    // A decay this fast takes scores and values out of range as a rule; otherwise the split walk finds out.
+    bool fp32 = far < 0x1p-20f && __builtin_amdgcn_readfirstlane(sm.pw[1] > 0.0f);
+    if (!fp32 && walk_split()) {
+        load_qk(tok_begin);
+        load_v(tok_begin);
+        enter_state();
+        fp32 = true;
     }
+    if (fp32) walk_fp32();
 
     float* dst = nullptr;
     if (kOut) {

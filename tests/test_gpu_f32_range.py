@@ -33,7 +33,7 @@ def _run(B, q, k, v, gamma, state=None, segments=0):
     return out.cpu().numpy(), s_out.cpu().numpy()
 
 
-@pytest.mark.parametrize("d", [64])
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("segments", [1, 3])
 @pytest.mark.parametrize("where", ["q", "k", "v", "state"])
 def test_an_infinity_reaches_what_it_should_as_an_infinity(B, d, segments, where):
@@ -71,7 +71,7 @@ def test_an_infinity_reaches_what_it_should_as_an_infinity(B, d, segments, where
         assert np.abs(got[fin] - ref[fin]).max() <= 4e-6 * np.abs(ref[fin]).max()
 
 
-@pytest.mark.parametrize("d", [64])
+@pytest.mark.parametrize("d", [64, 128])
 def test_values_next_to_the_largest_float(B, d):
     # o = (q . k) v with one-hot rows: 1 * v is v, 2 * v overflows; nothing else of the job is touched
     N, big = 70, 3.4e38
@@ -89,7 +89,7 @@ def test_values_next_to_the_largest_float(B, d):
     assert np.array_equal(s, want_s)
 
 
-@pytest.mark.parametrize("d", [64])
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("scales", [(-60, -60, 104), (-118, 60, 50), (40, -112, 60), (60, 56, -118), (0, 0, -116)])
 def test_small_operands_keep_their_bits(B, d, scales):
     # powers of two move the exponents only; the same bound as at the usual sizes.  Nothing underflows: the
@@ -100,4 +100,32 @@ def test_small_operands_keep_their_bits(B, d, scales):
     out, s = _run(B, q, k, v, gamma)
     errs = max_rel_err(out, ref), max_rel_err(s, s_ref)
     print(f"  d {d} scales {scales}: out {errs[0]:.2e} state {errs[1]:.2e}", flush=True)
+    assert max(errs) <= 2e-6
+
+
+@pytest.mark.parametrize("how", ["fast decay", "one small value", "one large value"])
+@pytest.mark.parametrize("N,segments", [(1, 1), (31, 1), (32, 1), (33, 1), (63, 1), (65, 2), (97, 2), (200, 4), (700, 1), (700, 0),
+                                        (1100, 17), (2304, 9)])
+def test_width_128_on_fp32_matrix_instructions(B, N, segments, how):
+    """Every shape of the walk that width 128 falls back to: edges of the 32-token tiles, one and several segments
+    (whose states the walk combines itself, or the scan), the state handed on in place."""
+    gamma = torch.tensor([0.3, 0.0, 0.02]) if how == "fast decay" else torch.tensor([0.875, 0.97, 1.0])
+    q, k, v, gamma = W.make_custom_forward_inputs(2, 3, N, 128, "f32", seed=3000 + N, gamma=gamma)
+    state = torch.randn((2, 3, 128, 128), generator=torch.Generator().manual_seed(N)) * 0.1
+    if how == "one small value":
+        v[:, :, [0, N - 1], 77] = 2.0 ** -100
+    elif how == "one large value":  # the sum of the outputs' magnitudes overflows, no output does
+        v[:, :, N // 2, 77], k[:, :, N // 2], q[:, :, N // 2:, :] = 3e38, 0.25, 0.0
+        q[:, :, N // 2:, 5], k[:, :, N // 2, 5] = 1.0, 1.0
+    ref, s_ref = oracle.recurrent(*(W.to_f64(t) for t in (q, k, v, gamma)), W.to_f64(state))
+    S = state.cuda()
+    out = B.leet_attn_forward_v2(q.cuda(), k.cuda(), v.cuda(), gamma.cuda(), state_in=S, state_out=S, segments=segments)
+    if how == "one large value":  # column 77 by itself, the others by theirs
+        out, ref, S, s_ref = (np.swapaxes(np.asarray(t.cpu() if torch.is_tensor(t) else t, dtype=np.float64), 1, 3)
+                              for t in (out, ref, S, s_ref))
+        out, ref, S, s_ref = (t.reshape(t.shape[0], 128, -1) for t in (out, ref, S, s_ref))
+        errs = max_rel_err(out, ref), max_rel_err(S, s_ref)
+    else:
+        errs = max_rel_err(out.cpu().numpy(), ref), max_rel_err(S.cpu().numpy(), s_ref)
+    print(f"  N {N} segments {segments} {how}: out {errs[0]:.2e} state {errs[1]:.2e}", flush=True)
     assert max(errs) <= 2e-6
