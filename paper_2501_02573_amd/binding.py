@@ -191,6 +191,13 @@ def _call(fn, dev: torch.device, *args) -> int:
         return fn(*args, _raw_stream(index))
 
 
+def _new_out(like: torch.Tensor, dtype: torch.dtype) -> torch.Tensor:
+    """A fresh dense tensor of ``like``'s shape and device: strides and class are not taken over."""
+    if type(like) is torch.Tensor:  # 2 us less than torch.empty
+        return torch.empty_like(like, dtype=dtype, memory_format=torch.contiguous_format)
+    return torch.empty(like.shape, dtype=dtype, device=like.device)
+
+
 KERNEL_WIDE, KERNEL_COLUMN_SPLIT, KERNEL_AUTO = 0, 1, 2
 
 
@@ -262,7 +269,7 @@ def leet_attn_forward(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, gamma: 
                       out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Chunked prefill with zero initial state; returns fp32 ``out`` [B, H, N, d]."""
     if out is None:
-        out = torch.empty_like(q, dtype=torch.float32)
+        out = _new_out(q, torch.float32)
     B, H, N, d = _check_forward(q, k, v, gamma, out)
     dev = _check_dev(q, k, v, gamma, out)
     st = _call(lib.leet_attn_forward, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), B, H, N, d,
@@ -278,7 +285,7 @@ def leet_attn_forward_ex(q, k, v, gamma, out: Optional[torch.Tensor] = None,
                          workspace: Optional[torch.Tensor] = None, segments: int = 0) -> torch.Tensor:
     """Chunked prefill with state hand-off and optional caller-owned workspace."""
     if out is None:
-        out = torch.empty_like(q, dtype=torch.float32)
+        out = _new_out(q, torch.float32)
     B, H, N, d = _check_forward(q, k, v, gamma, out)
     for name, s in (("state_in", state_in), ("state_out", state_out)):
         if s is not None and (s.dtype != torch.float32 or tuple(s.shape) != (B, H, d, d)):
@@ -309,7 +316,7 @@ def leet_attn_forward_v2(q, k, v, gamma: Optional[torch.Tensor], out: Optional[t
     ``mask=LEET_MASK_CAUSAL``.  Unsupported combinations are reported by the library.
     """
     if out is None:
-        out = torch.empty_like(q, dtype=out_dtype or torch.float32)
+        out = _new_out(q, out_dtype or torch.float32)
     B, H, N, d = _check_forward(q, k, v, gamma, out, any_out_dtype=True)
     for name, s in (("state_in", state_in), ("state_out", state_out)):
         if s is not None and (s.dtype != torch.float32 or tuple(s.shape) != (B, H, d, d)):
@@ -334,7 +341,7 @@ def leet_attn_forward_recurrent(q, k, v, gamma: Optional[torch.Tensor], out: Opt
                                 mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """Row-based (token-by-token) prefill on the GPU: the comparison point for the chunked path."""
     if out is None:
-        out = torch.empty_like(q, dtype=torch.float32)
+        out = _new_out(q, torch.float32)
     B, H, N, d = _check_forward(q, k, v, gamma, out)
     for name, s in (("state_in", state_in), ("state_out", state_out)):
         if s is not None and (s.dtype != torch.float32 or tuple(s.shape) != (B, H, d, d)):
@@ -350,7 +357,7 @@ def leet_attn_forward_recurrent(q, k, v, gamma: Optional[torch.Tensor], out: Opt
 def leet_attn_forward_profile(q, k, v, gamma, out: Optional[torch.Tensor] = None, segments: int = 0):
     """One prefill with per-kernel HIP-event timing; returns (out, [pre-pass ms, scan ms, walk ms])."""
     if out is None:
-        out = torch.empty_like(q, dtype=torch.float32)
+        out = _new_out(q, torch.float32)
     B, H, N, d = _check_forward(q, k, v, gamma, out)
     dev = _check_dev(q, k, v, gamma, out)
     ms = (ctypes.c_float * 3)()
@@ -393,7 +400,7 @@ def leet_attn_decode_step(q, k, v, gamma, state, out: Optional[torch.Tensor] = N
     if q.dtype != torch.bfloat16:
         raise TypeError("leet_attn_decode_step takes bfloat16 q, k, v (use leet_attn_decode_step_ex for float32)")
     if out is None:
-        out = torch.empty_like(q, dtype=torch.float32)
+        out = _new_out(q, torch.float32)
     B, H, d = _check_decode(q, k, v, gamma, state, out)
     dev = _check_dev(q, k, v, gamma, state, out)
     st = _call(lib.leet_attn_decode_step, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
@@ -406,7 +413,7 @@ def leet_attn_decode_step(q, k, v, gamma, state, out: Optional[torch.Tensor] = N
 def leet_attn_decode_step_ex(q, k, v, gamma, state, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """One decode step with float32 or bfloat16 q, k, v."""
     if out is None:
-        out = torch.empty_like(q, dtype=torch.float32)
+        out = _new_out(q, torch.float32)
     B, H, d = _check_decode(q, k, v, gamma, state, out)
     dev = _check_dev(q, k, v, gamma, state, out)
     st = _call(lib.leet_attn_decode_step_ex, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
@@ -420,7 +427,7 @@ def leet_attn_decode_step_v2(q, k, v, gamma: Optional[torch.Tensor], state, out:
                              mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """One decode step with float32, bfloat16 or float16 q, k, v and either mask."""
     if out is None:
-        out = torch.empty_like(q, dtype=torch.float32)
+        out = _new_out(q, torch.float32)
     B, H, d = _check_decode(q, k, v, gamma, state, out)
     dev = _check_dev(q, k, v, gamma, state, out)
     st = _call(lib.leet_attn_decode_step_v2, dev, _ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(state), _ptr(out),
@@ -461,7 +468,7 @@ def leet_attn_forward_rd(q, k, v, gamma: Optional[torch.Tensor], out: Optional[t
                          out_dtype: Optional[torch.dtype] = None, mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """Chunked prefill with q, k of width r and v, out of width dv; states are [B, H, r, dv]."""
     if out is None:
-        out = torch.empty_like(v, dtype=out_dtype or torch.float32)
+        out = _new_out(v, out_dtype or torch.float32)
     B, H, N, r, dv = _check_rd(q, k, v, gamma, out, True)
     _check_states_rd(B, H, r, dv, state_in=state_in, state_out=state_out)
     ws_bytes = 0
@@ -485,7 +492,7 @@ def leet_attn_forward_v3(q, k, v, gamma: Optional[torch.Tensor], out: Optional[t
                          out_dtype: Optional[torch.dtype] = None, mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """``leet_attn_forward_rd`` with the kernel choice given per call."""
     if out is None:
-        out = torch.empty_like(v, dtype=out_dtype or torch.float32)
+        out = _new_out(v, out_dtype or torch.float32)
     B, H, N, r, dv = _check_rd(q, k, v, gamma, out, True)
     _check_states_rd(B, H, r, dv, state_in=state_in, state_out=state_out)
     ws_bytes = 0
@@ -582,7 +589,7 @@ def leet_attn_forward_recurrent_rd(q, k, v, gamma: Optional[torch.Tensor], out: 
                                    mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """Row-based prefill with q, k of width r and v, out of width dv."""
     if out is None:
-        out = torch.empty_like(v, dtype=torch.float32)
+        out = _new_out(v, torch.float32)
     B, H, N, r, dv = _check_rd(q, k, v, gamma, out, False)
     _check_states_rd(B, H, r, dv, state_in=state_in, state_out=state_out)
     dev = _check_dev(q, k, v, gamma, out, state_in, state_out)
@@ -599,7 +606,7 @@ def leet_attn_forward_fleet(q, k, v, gamma: Optional[torch.Tensor], out: Optiona
                             mask: int = LEET_MASK_DECAY) -> torch.Tensor:
     """FleetAttention prefill (rank-sum of discounted cumulative sums); q, k [B, H, N, r], v [B, H, N, dv]."""
     if out is None:
-        out = torch.empty_like(v, dtype=torch.float32)
+        out = _new_out(v, torch.float32)
     B, H, N, r, dv = _check_rd(q, k, v, gamma, out, False)
     _check_states_rd(B, H, r, dv, state_in=state_in, state_out=state_out)
     dev = _check_dev(q, k, v, gamma, out, state_in, state_out)
@@ -623,7 +630,7 @@ def leet_attn_decode_step_rd(q, k, v, gamma: Optional[torch.Tensor], state, out:
     B, H, r = q.shape
     dv = v.shape[2]
     if out is None:
-        out = torch.empty_like(v, dtype=torch.float32)
+        out = _new_out(v, torch.float32)
     if gamma is not None and (gamma.dtype != torch.float32 or gamma.numel() != H):
         raise ValueError("gamma must be float32 with one value per head")
     _check_states_rd(B, H, r, dv, state=state)
