@@ -533,7 +533,7 @@ class PreparedForward:
         self._args = (_ptr(q), _ptr(k), _ptr(v), _ptr(gamma), _ptr(out), _ptr(state_in), _ptr(state_out),
                       _ptr(workspace), ws_bytes, int(segments), int(kernel), B, H, N, r, dv,
                       _dtype_code(q), _dtype_code(out), int(mask))
-        self._stream = None if stream is None else int(stream)
+        self._stream = None if stream is None else ctypes.c_void_p(stream)  # refuses what is not a handle
         self._fn = lib.leet_attn_forward_v3
         self.out = out
 

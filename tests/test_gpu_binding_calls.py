@@ -1,6 +1,8 @@
-"""What the binding hands out and takes, whatever the layout and type of its arguments."""
+"""What the binding hands out and refuses, whatever the layout and type of its arguments."""
 import pytest
 import torch
+
+from paper_2501_02573_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +59,23 @@ def test_outputs_are_plain_tensors(B):
     x = [torch.randn((2, 1, 1, 64), device="cuda").bfloat16().as_subclass(Named) for _ in range(3)]
     for n, out in enumerate(_entry_points(B, *x, torch.full((1,), 0.9, device="cuda"))):
         assert type(out) is torch.Tensor, n
+
+
+@pytest.mark.parametrize("stream", ["0", 0.0, 1.5, b"0"])
+def test_a_prepared_call_takes_a_stream_handle_only(B, stream):
+    q, k, v, gamma = (t.cuda() for t in W.make_custom_forward_inputs(1, 1, 8, 64, "bf16", seed=1))
+    out = torch.empty((1, 1, 8, 64), device="cuda")
+    with pytest.raises(TypeError):
+        B.PreparedForward(q, k, v, gamma, out, stream=stream)
+
+
+def test_a_prepared_call_runs_on_the_stream_it_was_given(B):
+    q, k, v, gamma = (t.cuda() for t in W.make_custom_forward_inputs(1, 4, 300, 64, "bf16", seed=2))
+    want = B.leet_attn_forward(q, k, v, gamma)
+    stream = torch.cuda.Stream()
+    for handle in (stream.cuda_stream, 0):
+        out = torch.zeros_like(want)
+        torch.cuda.synchronize()
+        B.PreparedForward(q, k, v, gamma, out, stream=handle)()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
