@@ -179,7 +179,9 @@ def _ptr(t: Optional[torch.Tensor]):
 # with a device guard, a Stream object and a c_void_p per argument; 9.1 us as below): the device
 # guard is entered only where it would change the device, the stream is taken as the raw handle, and
 # addresses travel as plain integers.
-_raw_stream = torch._C._cuda_getCurrentRawStream
+# The raw handle's call is private to torch; where it is missing, the public one makes an object for it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
 def _call(fn, dev: torch.device, *args) -> int:
