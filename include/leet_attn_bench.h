@@ -15,12 +15,13 @@ extern "C" {
 
 /*
  * Computes what leet_attn_forward_ex computes (Alg. 2 with the decaying mask of Eq. "BCMV"), with
- * HIP events recorded on `stream` around each of the three kernels a prefill launches; the call
- * waits for them.  The pre-pass and the walk (which write the same values each time) are launched
- * five times back to back between their events and the time is divided by five; the scan runs once.
+ * HIP events recorded on `stream` around each kernel the prefill launches (one without segments;
+ * with them three, or two where the fp32 walk combines the segment states itself); the call waits
+ * for them.  The pre-pass and the walk (which write the same values each time) are launched five
+ * times back to back between their events and the time is divided by five; the scan runs once.
  *   kernel_ms  HOST pointer to 3 floats, filled with the milliseconds per launch of
  *              [0] the segment-state pre-pass, [1] the segment scan, [2] the chunk walk
- *              ([0] and [1] are 0 when the plan has a single segment).
+ *              (0 for a kernel that the plan does not launch).
  * state_out must not alias state_in here (LEET_ERR_INVALID_ARG): the repeated launches would
  * start from the state the first one left.
  * Synchronous (returns after the work has finished); not for use under graph capture.

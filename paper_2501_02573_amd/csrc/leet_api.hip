@@ -510,7 +510,9 @@ int forward_impl(const void* q, const void* k, const void* v, const float* gamma
     if (rc == LEET_OK) {
         kernel_ms[0] /= kProfileRepeat;
         kernel_ms[2] /= kProfileRepeat;
-        if (plan.nseg <= 1) kernel_ms[0] = kernel_ms[1] = 0.0f;  // nothing was launched in those slots
+        // nothing was launched in those slots
+        if (plan.nseg <= 1) kernel_ms[0] = 0.0f;
+        if (plan.nseg <= 1 || plan.fold) kernel_ms[1] = 0.0f;
     }
     for (int i = 0; i < 6; ++i) (void)hipEventDestroy(ev[i]);
     return rc;
