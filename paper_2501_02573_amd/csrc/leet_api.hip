@@ -72,9 +72,11 @@ struct Plan {
 };
 
 // fp32: a walk workgroup that enters segment s after s pre-pass states can read and combine those
-// states itself, which saves the scan kernel's launch and its pass over all states.  It pays while a
-// workgroup has at most this much to read: 3 states at d = 128 (B1 H32 N256: 26.2 -> 23.4 us; 7 states,
-// B1 H32 N512: 31.5 -> 36.3), 15 at d = 64 (3 states, B1 H1 N256: 13.9 -> 12.6, 15 states, B2 H8 N2048: 30.9 -> 29.5).
+// states itself, one after the other, which saves the scan kernel's launch and its pass over all states.
+// It pays while a workgroup has little to read (us a call, scan -> combined; B*H x N).  d = 64, states of
+// 16 KB: 3 of them (1 x 256) 14.3 -> 12.8, 7 (16 x 512) 17.7 -> 16.8 but (32 x 512) 19.5 -> 19.5, 15 (16 x 1024)
+// 22.0 -> 22.2, 24 (8 x 1600) 24.2 -> 25.2, 31 (8 x 2048) 27.3 -> 28.4.  d = 128, 64 KB: 3 (32 x 256) 29.3 -> 26.2,
+// 4 (32 x 320) 30.8 -> 29.5, 5 (32 x 384) 31.4 -> 30.6, 6 (32 x 448) 32.4 -> 32.1.  The line is where width 64 breaks even.
 constexpr size_t kFoldBytes = (size_t)240 << 10;
 
 // The pre-pass is a pure read stream and runs faster with two workgroups per compute unit
@@ -89,8 +91,10 @@ int wide_pre_split(long BH, int nseg, int seg_chunks) {
 // the 256 compute units: it runs on segments `split` times finer than the walk's, with the split
 // (1, 2, 4 or 8 parts of at least two chunks) that needs the fewest chunk-times -- rounds of 256
 // workgroups x chunks per workgroup, a tenth less once two workgroups share a compute unit and
-// overlap -- plus half a chunk-time per part for the longer scan (B4 H16 N4096 d128, whole call:
-// 223 us with 1 part, 219 with 2, 222 with 4; B1 H128 N8192 d64: 422, 368, 355).
+// overlap -- plus half a chunk-time per part for the longer scan.  us a call with 1, 2, 4, 8 parts, * the
+// rule's (B*H x N): d = 128: 64 x 4096 283 273 *283 294, 32 x 8192 273 *262 273 289, 128 x 8192 1006 *940 923 935,
+// 100 x 3000 376 *373 390 425, 8 x 16384 142 *149 172; d = 64: 64 x 4096 118 119 *117 125, 128 x 8192 467 *414 402 404,
+// 32 x 16384 242 234 237 *250, 16 x 8192 71 *76 87 (its one part would need no scan, which the rule does not count).
 int f32_pre_split(long BH, int nseg, int seg_chunks) {
     if (nseg <= 1) return 1;
     const long units = BH * (nseg - 1);
@@ -110,7 +114,8 @@ int f32_pre_split(long BH, int nseg, int seg_chunks) {
 // workgroup) and of its HBM/last-level-cache transfer time; a call is the sum of its kernels plus
 // a fixed cost per call.  The constants are a least-squares fit (5 % rms) to event-timed runs of
 // both kernels at 1 to 64 segments over B*H in 1..768 and N in 256..65536 (each of the three shapes); the tabulated runs are
-// kept with the profiles, and a host test checks the planner's picks against them.
+// kept with the profiles, and a host test checks the planner's picks against them.  Width 64: the runs of the
+// column-split kernel are from before its third loader stage, which is 4 to 7 % faster where inputs come from memory.
 struct CostModel {
     double wide_chunk_us, wide_pre_chunk_us;    // lone wide workgroup: walk and pre-pass per chunk
     double coop_chunk_us, coop_pre_chunk_us;    // column-split workgroups of one sequence, likewise
@@ -129,7 +134,7 @@ constexpr CostModel kCost64 = {1.839, 0.516, 0.546, 0.287, 7.540e6, 6.094e6, 8.0
 // rank 128, value width 256: one wide workgroup per compute unit (512 threads)
 constexpr CostModel kCost128x256 = {3.172, 1.643, 0.733, 0.427, 8.0e6, 6.706e6, 6.553e6, 4.692e6,
                                     4.32, 10.17, 0.426, 2.229, 2.0, 1.158, 256};
-constexpr double kOneKernelFloorUs = 11.0;    // shortest call seen end to end, one and three kernels
+constexpr double kOneKernelFloorUs = 11.0;    // shortest call in those runs, one and three kernels (host time is less now)
 constexpr double kThreeKernelFloorUs = 17.0;
 constexpr int kCoopSlots = 256;               // one column-split workgroup per compute unit
 

@@ -131,9 +131,10 @@ __device__ __forceinline__ f32x16 zero16() {
 // Two loader waves (four measured no faster) with two or three register stages each.  Over inputs that
 // come from memory the loads are bound by what a compute unit keeps in flight, so a third stage pays
 // where it costs nothing else: at D = 64, whose chunks are half the bytes (B8 H16 N4000 70.8 -> 67.7 us with
-// fp32 and 63.5 -> 60.1 with fp16 outputs, B1 H16 N16000 59.9 -> 55.8).  D = 128 keeps two: its row waves
-// fill the registers (B2 H16 N2048 29.1 against 29.7, B1 H32 N777 13.9 against 14.1; width 256, N2000 32.3
-// against 32.4).  Four spill at D = 128 and gain nothing more at 64.
+// fp32 and 63.5 -> 60.1 with fp16 outputs, B1 H16 N16000 59.9 -> 55.8).  At D = 128 the row waves fill the
+// registers, and a third stage pays for a few long sequences only (B1 H8 N8192 37.1 -> 34.7 us; B2 H16 N2048
+// 29.1 -> 29.7, B1 H32 N777 13.9 -> 14.1; width 256, N2000 32.3 -> 32.4): it keeps two.  Four spill at D = 128
+// and gain nothing more at 64.
 constexpr int kCoopLoaderWaves = 2;
 constexpr int coop_stages(int D) { return D == 64 ? 3 : 2; }
 constexpr int kCoopThreads = 384 + 64 * kCoopLoaderWaves;
