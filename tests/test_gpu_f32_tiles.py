@@ -1,5 +1,6 @@
-"""The fp32 chunk walk at the edges of its 32-token tiles, against the fp64 oracle, and what its
-three-term operands have to preserve: any exponent, and non-finite tokens kept from earlier ones."""
+"""The fp32 chunk walks at the edges of their tiles (32 tokens at width 128, 64 at width 64), against the fp64 oracle,
+exponents that move by powers of two, and non-finite tokens kept from earlier ones.  What lies outside the range
+of three-term operands is in test_gpu_f32_range.py."""
 import numpy as np
 import pytest
 import torch
@@ -10,8 +11,8 @@ from paper_2501_02573_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-# Products are exact to 2^-22; an output is the sum of two fp32 contractions (128 and 32 terms a tile,
-# fewer than 64 roundings at full size between them) of operands that carry as many again.  With random
+# Products round at 2^-24 (test_gpu_f32_products.py); an output is the sum of two fp32 contractions (128 and 32 terms a
+# tile, fewer than 64 roundings at full size between them) of operands that carry as many again.  With random
 # signs that is sqrt(128) * 2^-25 = 3.4e-7 of the head's largest value; six of that.  A partial product
 # left out (2^-16 to 2^-17 of a term) shows as 4e-6 and more.
 TOL = 2e-6
