@@ -427,8 +427,9 @@ def extra_legs(torch, binding, W, dev, cfg3, tokens3, use_graph):
     extra["decode_cold"]["default_store_policy"] = extra["decode_cold"]["by_store_policy"]["auto"]
     del S, qkv, o, cold
 
-    # ---- the fp32 kernel: config 2, and the headline shape with fp32 inputs.  Roofline: fp32 MFMA,
-    # priced with the flops the method needs (4 d^2 + 2*64*d per token-head), not the issued ones.
+    # ---- the fp32 kernels: config 2, and the headline shape with fp32 inputs.  Roofline: at d = 64 fp32
+    # MFMA; at d = 128 an fp32 product is eight bf16 MFMA products, so an eighth of that peak.  Priced
+    # with the flops the method needs (4 d^2 + 2*64*d per token-head), not the issued ones.
     extra["fp32"] = {}
     for cfgf in (W.CONFIG2, W.ForwardConfig("cfg3_shape_f32", cfg3.B, cfg3.H, cfg3.N, cfg3.d, "f32", cfg3.seed, cfg3.gamma_kind)):
         qf, kf, vf, gf = (t.to(dev) for t in W.make_forward_inputs(cfgf))
@@ -436,15 +437,17 @@ def extra_legs(torch, binding, W, dev, cfg3, tokens3, use_graph):
         msf = timed(lambda: binding.leet_attn_forward_ex(qf, kf, vf, gf, out=of), 100, 200)
         kmsf = kernel_times(binding, qf, kf, vf, gf, of, 10, 0)
         ff, bf = alg_flops_forward(cfgf), alg_bytes_forward(cfgf, 4)
+        split = cfgf.d == 128
+        peakf = MFMA_BF16_PEAK_TFLOPS / 8 if split else MFMA_FP32_PEAK_TFLOPS
         nsegf, _ = binding.query_plan(cfgf.B, cfgf.H, cfgf.N, cfgf.d, binding.LEET_F32)
         extra["fp32"][cfgf.name] = {
             "B": cfgf.B, "H": cfgf.H, "N": cfgf.N, "d": cfgf.d, "segments": nsegf, "steps": 200, "warmup": 100,
             "ms_per_step": msf, "tokens_per_s": cfgf.B * cfgf.N / (msf * 1e-3),
             "kernel_ms": {"segment_state_prepass": kmsf[0], "segment_scan": kmsf[1], "chunk_walk": kmsf[2]},
             "hbm_frac_whole_step": bf / (msf * 1e-3) / 1e9 / HBM_PEAK_GBS,
-            "roofline": {"kernel": f"fwd_f32_kernel<{cfgf.d}> (pre-pass + scan + walk: the whole step)", "bound": "mfma",
-                         "achieved": ff / (msf * 1e-3) / 1e12, "peak": MFMA_FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                         "frac": ff / (msf * 1e-3) / 1e12 / MFMA_FP32_PEAK_TFLOPS, "traffic": None,
+            "roofline": {"kernel": ("fwd_f32_split_kernel" if split else "fwd_f32_kernel") + " (all kernels of the step)", "bound": "mfma",
+                         "achieved": ff / (msf * 1e-3) / 1e12, "peak": peakf, "unit": "TFLOP/s",
+                         "frac": ff / (msf * 1e-3) / 1e12 / peakf, "traffic": None,
                          "algorithmic_flops_per_step": ff},
         }
         del qf, kf, vf, of
