@@ -19,7 +19,8 @@
 // Range: the bf16 matrix instructions take denormal terms and sums (below 2^-126) as zero, and an infinity leaves
 // x - x0 = NaN.  So the walk watches the smallest nonzero operands and whether its results are finite, and where
 // something is out of range the segment is walked again with fp32 matrix instructions (walk_fp32), whose
-// results stand for every operand.  Ordinary data never does that; the watching costs some 50 of 650 vector operations
+// results stand for every operand.  Ordinary data never does that (nor zeros behind a sequence: B4 H16 N4096, half of it
+// zeros, 252 us); the watching costs some 50 of 650 vector operations
 // a tile (B4 H16 N4096 273 -> 282 us; without it q, k ~ 2^-60 with v ~ 2^104 came out with errors of 6e-4).
 //
 // Work split: a column tile of 32 value columns belongs to two waves (in the pre-pass: one),
@@ -91,22 +92,27 @@ struct Smem {
     int bad[3];            // out of range: seen in even tiles, in odd tiles, in the whole walk
 };
 
-// Whether one of kN values is nonzero and below `least` in magnitude: twice the magnitude's bits minus one puts
-// zero above everything else.
+// The smallest magnitude of kN values; and of those other than zero, as twice its bits minus one, which puts zero
+// above everything else.  The first is half an operation a value and enough for data without zeros.
 template <int kN, class Get>
-__device__ __forceinline__ bool has_small_nonzero(Get x, float least) {
-    uint32_t m = ~0u;
-#pragma unroll
-    for (int i = 0; i < kN; ++i) m = min(m, (__float_as_uint(x(i)) << 1) - 1);
-    return m < (__float_as_uint(least) << 1) - 1;
-}
-// The same in half an operation a value for data without zeros: they are told apart only once the smallest is below.
-template <int kN, class Get>
-__device__ __forceinline__ bool has_small(Get x, float least) {
+__device__ __forceinline__ float smallest(Get x) {
     float m = __builtin_fabsf(x(0));
 #pragma unroll
     for (int i = 1; i < kN; ++i) m = __builtin_fminf(m, __builtin_fabsf(x(i)));
-    return __any(m < least) ? has_small_nonzero<kN>(x, least) : false;
+    return m;
+}
+__device__ __forceinline__ uint32_t rank_nonzero(float x) { return (__float_as_uint(x) << 1) - 1; }
+template <int kN, class Get>
+__device__ __forceinline__ uint32_t smallest_nonzero(Get x) {
+    uint32_t m = ~0u;
+#pragma unroll
+    for (int i = 0; i < kN; ++i) m = min(m, rank_nonzero(x(i)));
+    return m;
+}
+// Whether one of them is nonzero and below `least`.
+template <int kN, class Get>
+__device__ __forceinline__ bool has_small(Get x, float least) {
+    return __any(smallest<kN>(x) < least) ? smallest_nonzero<kN>(x) < rank_nonzero(least) : false;
 }
 // 2^e as a float, -126 <= e <= 127
 __device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
@@ -410,8 +416,15 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
                 __syncthreads();  // the previous tile's sums visible; everyone is done reading its planes and scores
                 store_out(tok0 - kTile);
             }
-            constexpr int NS = kOut ? 16 * DT : 0;  // values of S, which is an operand in G3 only
-            bad |= has_small<NS + 4 * NLOAD>([&](int x) { return x < NS ? S[x / 16 % DT][x % 16] : rk[(x - NS) / 4 % NLOAD][x % 4]; }, least_k);
+            auto k_at = [&](int x) { return rk[x / 4][x % 4]; };
+            auto s_at = [&](int x) { return S[x / 16][x % 16]; };
+            float least_seen = smallest<4 * NLOAD>(k_at);
+            if (kOut) least_seen = __builtin_fminf(least_seen, smallest<16 * DT>(s_at));  // S is an operand in G3 only
+            uint32_t s_small = ~0u;
+            if (__any(least_seen < least_k)) {
+                bad |= smallest_nonzero<4 * NLOAD>(k_at) < rank_nonzero(least_k);
+                if (kOut) s_small = smallest_nonzero<16 * DT>(s_at);
+            }
             if (kOut) bad |= has_small<4 * NLOAD>([&](int x) { return rq[x >> 2][x & 3]; }, least_q);
 #pragma unroll
             for (int r = 0; r < NLOAD; ++r) {
@@ -425,6 +438,21 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
             // a condition, every later wait would have to cover the path without them and so drain them.)
             load_qk(next);
             __builtin_amdgcn_sched_barrier(0);
+            // A state that has decayed below its least magnitude is held against the rows of q that it meets: with
+            // tokens of zeros behind a sequence there are none.
+            if (kOut && __any(s_small < rank_nonzero(least_k))) {
+                uint32_t q_small = ~0u;
+#pragma unroll
+                for (int i = 0; i < 2 * DT; ++i) {
+                    const u32x4 x = *reinterpret_cast<const u32x4*>(&sm.q[q_row32 + 16 * i]);  // upper halves
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) q_small = min(q_small, min((x[e] << 17) - 1, ((x[e] & 0xffff0000u) << 1) - 1));
+                }
+#pragma unroll
+                for (int m = 1; m < 64; m *= 2) q_small = min(q_small, (uint32_t)__shfl_xor((int)q_small, m));
+                const float sv = __uint_as_float((s_small + 1) >> 1), qv = __uint_as_float((q_small + 1) >> 1);
+                bad |= s_small != ~0u && q_small != ~0u && (sv < 0x1p-100f || sv * qv < 0x1p-96f);
+            }
 
             f32x16 o, os;  // leading products, the others
             if (kOut) {
@@ -455,7 +483,7 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
                         const bool below = n == 1 || l16 >= q4 + 4 * r;  // on or below the diagonal
                         m[r] = below ? (big[r] + small[r]) * wgt[r] : 0.0f;
                     }
-                    bad |= has_small_nonzero<4>([&](int x) { return m[x]; }, least_p);
+                    bad |= smallest_nonzero<4>([&](int x) { return m[x]; }) < rank_nonzero(least_p);
                     store4(sm.p + (16 * it + l16) * RP + 16 * jt + 4 * q4, kTile * RP, m[0], m[1], m[2], m[3]);
                 }
 

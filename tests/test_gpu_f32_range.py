@@ -129,3 +129,23 @@ def test_width_128_on_fp32_matrix_instructions(B, N, segments, how):
         errs = max_rel_err(out.cpu().numpy(), ref), max_rel_err(S.cpu().numpy(), s_ref)
     print(f"  N {N} segments {segments} {how}: out {errs[0]:.2e} state {errs[1]:.2e}", flush=True)
     assert max(errs) <= 2e-6
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("segments", [1, 5])
+def test_a_state_that_decays_away(B, d, segments):
+    # 200 tokens, then k = v = 0 for long: the state passes every magnitude down to zero, and rows of q that meet it
+    # must give it back.  Every entry is positive, so an output errs by what its state does: one rounding (2^-24) a tile of 32
+    # tokens, and half a unit of gamma^32 as it enters each of them, over 122 tiles; a few more at the end.
+    N = 3900
+    q, k, v, gamma = W.make_custom_forward_inputs(1, 2, N, d, "f32", seed=40 + d, gamma=torch.tensor([0.97, 0.985]))
+    q, k, v = (t.abs() + 2.0 ** -10 for t in (q, k, v))
+    k[:, :, 200:], v[:, :, 200:] = 0.0, 0.0
+    q[:, :, 2000:2100] = 0.0
+    ref, s_ref = oracle.recurrent(*(W.to_f64(t) for t in (q, k, v, gamma)))
+    out, s = _run(B, q, k, v, gamma, segments=segments)
+    big = ref > 2.0 ** -118
+    err = np.abs(out[big] / ref[big] - 1).max()
+    print(f"  d {d} segments {segments}: {err:.2e} down to {ref[big].min():.1e}", flush=True)
+    assert big.mean() > 0.5 and err <= (1.5 * N / 32 + 8) * 2.0 ** -24
+    assert (out[:, :, 2000:2100] == 0).all() and np.abs(out[~big] - ref[~big]).max() <= 2.0 ** -118
