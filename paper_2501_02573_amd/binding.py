@@ -193,10 +193,13 @@ def _call(fn, dev: torch.device, *args) -> int:
         return fn(*args, _raw_stream(index))
 
 
+_Tensor, _empty_like, _dense = torch.Tensor, torch.empty_like, torch.contiguous_format
+
+
 def _new_out(like: torch.Tensor, dtype: torch.dtype) -> torch.Tensor:
     """A fresh dense tensor of ``like``'s shape and device: strides and class are not taken over."""
-    if type(like) is torch.Tensor:  # 2 us less than torch.empty
-        return torch.empty_like(like, dtype=dtype, memory_format=torch.contiguous_format)
+    if type(like) is _Tensor:  # 2 us less than torch.empty
+        return _empty_like(like, dtype=dtype, memory_format=_dense)
     return torch.empty(like.shape, dtype=dtype, device=like.device)
 
 
