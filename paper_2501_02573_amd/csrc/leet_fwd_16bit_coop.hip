@@ -25,9 +25,8 @@
 //                G2  O^T += V^T P^T (V through transposing LDS reads, P^T straight from the G1
 //                    accumulators: a P^T accumulator, lane = query, registers = keys, is a B operand
 //                    as it is); the finished tile goes to LDS for the store wave.
-//                The Q rows of a row block are used by this wave alone, so they never enter LDS:
-//                the wave loads its own operand fragments from global memory into registers, one
-//                chunk ahead, and uses them for all three products.
+//                The Q rows of a row block are used by this wave alone, each fragment for all three
+//                products: the lower wave loads them into registers, the upper one has an LDS tile of its own.
 //   waves 2, 3   G4  S[dk tile][c] = gamma^L S + K^T (Gam V) for two of the four 32-row state tiles
 //                    each (one of two at d = 64), A = K through transposing reads, B = the Gam-scaled
 //                    V copy, read once for both tiles; the owner keeps its fp32 tiles in accumulators
@@ -45,8 +44,14 @@
 // the compute waves run, and the only thing that ties the two together is one workgroup
 // barrier per chunk.  The chunk is software-pipelined over that barrier: in iteration t the row
 // waves produce O(t), the state waves S(t+1), the store waves write chunk t-1 to memory, and
-// the loaders write chunk t+1 to LDS and issue the loads of chunk t+3 (t+4 with three stages).  The K tile, S^T and the
-// output tiles are double-buffered in LDS, the V slice and its scaled copy triple-buffered.
+// the loaders write chunk t+1 to LDS and issue the loads of chunk t+3 (t+4 with three stages).  The K tile, the V slice,
+// its scaled copy, S^T and the output tiles are double-buffered in LDS, the upper row block's Q has four stages.
+//
+// What bounds it over inputs that come from memory (B4 H16 N4096, width 128, 77 us): a compute unit's loads return in
+// order and only some 50 KB of them can be in flight, so the slices' shared reads of Q and K cost their full latency in
+// every slice: the same 201 MB take 51 us in this placement and 32 us where each compute unit reads a part of its own
+// (stores alone 25 us, no loads 27, all without compute 73).  For the same reason a load that warms L2 for the other slices
+// holds up its own compute unit's loads behind it and gains nothing, and neither do more stages.
 //
 // MFMA conventions (32x32x16): an A (B) operand holds, in lane l, row (column) l%32 and the
 // eight contraction slots of group g = l/32; an accumulator holds, in lane l, column l%32
@@ -66,7 +71,7 @@ namespace leet {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-template <int D>
+template <int D, bool kOut>
 struct CoopSmem {
     static constexpr int RSQ = D + 8;   // Q, K row stride (elements): 16-byte row reads spread over the banks
     // V slice, 32 columns, unpadded: the 4 rows x 32 B that 32 lanes of a transposing read touch
@@ -75,9 +80,15 @@ struct CoopSmem {
     static constexpr int RSV = 32;
     static constexpr int RSVS = 40;
     static constexpr int RST = D + 8;   // S^T[c][dk]
+    // Q of the upper row block, [stage]: filled by loads that write 16 bytes a lane in lane order, so the rows are unpadded;
+    // 16-byte piece p of row r sits at piece p ^ swizzle(r), so that a fragment read (one piece of 16 rows) meets every
+    // bank once.  First in the struct: these loads take their LDS address from 16 bits.
+    static constexpr int QS = kOut ? 4 : 1;
+    static __device__ __forceinline__ int swizzle(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
+    uint16_t q[QS][kOut ? 32 * D : 8];
     uint16_t k[2][kChunk * RSQ];
-    uint16_t v[3][kChunk * RSV];
-    uint16_t vs[3][kChunk * RSVS];      // Gam V: row j scaled by gamma^(63-j)
+    uint16_t v[2][kChunk * RSV];
+    uint16_t vs[2][kChunk * RSVS];      // Gam V: row j scaled by gamma^(63-j)
     uint16_t st[2][32 * RST];
     float obuf[2][2][32 * 36];          // finished O tiles on their way out: [buffer][row block][row][column], padded rows
     float pw[kChunk + 4];               // gamma^n, n = 0..64
@@ -124,6 +135,13 @@ __device__ __forceinline__ f32x16 zero16() {
     return z;
 }
 
+// a wave-uniform address in scalar registers, whatever the compiler has it in
+__device__ __forceinline__ const uint16_t* uniform_ptr(const uint16_t* p) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return reinterpret_cast<const uint16_t*>(((uint64_t)hi << 32) | lo);
+}
+
 }  // namespace coop
 
 // kOut = true : full walk (outputs + state).   kOut = false : state only (segment pre-pass).
@@ -154,8 +172,9 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     constexpr int PR = D / 8;      // 16-byte pieces per Q/K row
     constexpr int QPL = kChunk * PR / NL;  // Q (and K) pieces per loader thread per chunk
     constexpr int RPL = NL / PR;   // rows between two pieces of one loader thread
-    constexpr int RSQ = CoopSmem<D>::RSQ, RSV = CoopSmem<D>::RSV, RSVS = CoopSmem<D>::RSVS, RST = CoopSmem<D>::RST;
-    __shared__ __attribute__((aligned(16))) CoopSmem<D> sm;
+    typedef CoopSmem<D, kOut> Smem;
+    constexpr int RSQ = Smem::RSQ, RSV = Smem::RSV, RSVS = Smem::RSVS, RST = Smem::RST;
+    __shared__ __attribute__((aligned(16))) Smem sm;
 
     // Block -> (sequence segment, column slice).  Consecutive block ids go round-robin over
     // the 8 XCDs; the SL slices of one segment take ids that are equal modulo 8, so they share
@@ -234,6 +253,9 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     // ---- loaders: thread -> pieces.  Q, K: piece m is row m RPL + lt/PR, 16 bytes at column
     // 8 (lt%PR); V slice: piece m is row 32 m + lt/4, 16 bytes at column c0 + 8 (lt%4).
     const int qk_row = lt / PR, qk_cc = lt % PR;
+    // The slices of a sequence run in step and want the same K and Q lines; each begins at another row (Q likewise), so
+    // that they do not ask one L2 channel for one line at one time (both through LDS, B4 H16 N4096 cold: 78.3 -> 76.3 us).
+    auto piece = [&](int m) { return (m + slice * QPL / SL) % QPL; };
     const int v_row = lt >> 2, v_cc = lt & 3;
     const int qk_loff = qk_row * RSQ + qk_cc * 8;
     const int v_loff = v_row * RSV + v_cc * 8, vs_loff = v_row * RSVS + v_cc * 8;
@@ -258,7 +280,7 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
         const uint16_t* vc = vg + tok0 * DV;
 #pragma unroll
         for (int m = 0; m < QPL; ++m) {
-            const int row = max(qk_row + m * RPL - shift, 0);
+            const int row = max(qk_row + piece(m) * RPL - shift, 0);
             const unsigned off = (unsigned)(row * D + qk_cc * 8);
             st.k[m] = *reinterpret_cast<const u32x4*>(kc + off);
         }
@@ -276,19 +298,19 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     for (int m = 0; m < VPL; ++m) v_scale[m] = 0.0f;
     auto store_tiles = [&](Stage& st, int c) {
         const int shift = (c == n - 1) ? last_shift : 0;
-        const int qb = c & 1, vb = c % 3;
+        const int qb = c & 1, vb = c & 1;
         if (shift) {  // ragged last chunk: zero the rows that hold no token
             const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int m = 0; m < QPL; ++m)
-                if (qk_row + m * RPL < shift) st.k[m] = z;
+                if (qk_row + piece(m) * RPL < shift) st.k[m] = z;
 #pragma unroll
             for (int m = 0; m < VPL; ++m)
                 if (v_row + VRS * m < shift) st.v[m] = z;
         }
 #pragma unroll
         for (int m = 0; m < QPL; ++m) {
-            *reinterpret_cast<u32x4*>(&sm.k[qb][qk_loff + m * RPL * RSQ]) = st.k[m];
+            *reinterpret_cast<u32x4*>(&sm.k[qb][qk_loff + piece(m) * RPL * RSQ]) = st.k[m];
         }
 #pragma unroll
         for (int m = 0; m < VPL; ++m) {
@@ -342,7 +364,7 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
         const int shift = (t == n - 1) ? last_shift : 0;
         u32x4 ak[TPW][4], bv[4];
         const uint16_t* k_tr = &sm.k[qb][tr_off_k];
-        const uint16_t* vs_tr = &sm.vs[t % 3][tr_off_vs];
+        const uint16_t* vs_tr = &sm.vs[qb][tr_off_vs];
 #pragma unroll
         for (int f = 0; f < 4; ++f) {
             bv[f] = frag_tr(vs_tr + f * RSVS, 32 * RSVS);
@@ -365,31 +387,48 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     //       row block, the tile (0, 1) under the diagonal
     //   G3  O^T = S^T Q^T, rows scaled by gamma^(i+1)
     //   G2  O^T += V^T P^T over the keys of the tiles, then the tile goes to LDS for the store wave
-    // Q rows of a row block are used by that block's row wave only, so they do not pass through LDS:
-    // the wave loads its own B-operand fragments (lane = query row, 16 bytes at column 16 s + 8 g)
-    // straight from global memory into registers, one chunk ahead.
-    auto load_q = [&](u32x4 (&qn)[D / 16], int c, int it) {
+    // Q rows of a row block are used by that block's row wave only.  The lower wave, whose chain of products is the
+    // longest of the workgroup, loads its B-operand fragments (lane = query row, 16 bytes at column 16 s + 8 g) from global
+    // memory into registers, one chunk ahead: no LDS read stands before its first product.  Such a load touches 32 rows of
+    // 32 bytes, and in both waves these loads took half of the time of all loads over cold inputs (B4 H16 N4096: 64.6 us
+    // with them, 34.9 without Q).  So the upper wave fills stages of a Q tile of its own, by loads of whole rows straight
+    // from global memory to LDS, three chunks ahead, and waits for them by its own count of outstanding loads.
+    // us at B4 H16 N4096 in cache / cold, N2000 of width 256: both in registers 64.2 / 82.5, 32.8 / 40.2; both through LDS
+    // 67.7 / 76.9, 34.8 / 39.4 (its reads and writes add to the busiest unit); the upper one 63.4 / 77.7, 32.9 / 38.5.
+    auto load_q = [&](u32x4 (&qn)[D / 16], int c) {   // lower row block
         c = min(c, n - 1);
         const int shift = (c == n - 1) ? last_shift : 0;
-        const uint16_t* qrow = qg + ((size_t)(tok_begin + c * kChunk) + max(32 * it + ln - shift, 0)) * D + 8 * g;
+        const uint16_t* qrow = qg + ((size_t)(tok_begin + c * kChunk) + max(32 + ln - shift, 0)) * D + 8 * g;
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) qn[s] = *reinterpret_cast<const u32x4*>(qrow + 16 * s);
     };
+    constexpr int QI = D / 16;           // load instructions per row block, to LDS
+    constexpr int RPI = 64 / PR;         // rows per instruction
+    auto issue_q = [&](int c, int s) {   // upper row block, instruction s of chunk c
+        const int stage = c % Smem::QS;
+        c = min(c, n - 1);
+        const int shift = (c == n - 1) ? last_shift : 0;
+        const uint16_t* qc = uniform_ptr(qg + (size_t)(tok_begin + c * kChunk) * D);
+        const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&sm.q[stage][0] + 1024 * s;
+        const int r = RPI * s + l / PR;   // row of the block; rows above a ragged chunk's first token re-read that token
+        const unsigned off = (unsigned)(max(r - shift, 0) * D + 8 * ((l % PR) ^ Smem::swizzle(r))) * 2;
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(qc) : "memory");
+    };
+    // qf: the fragments of this chunk (lower: loaded before, upper: read here); qn: where the lower wave's next ones go
     auto row_block = [&](int t, auto lower, u32x4 (&qf)[D / 16], u32x4 (&qn)[D / 16]) {
         constexpr bool kLower = decltype(lower)::value;
         constexpr int IT = kLower ? 1 : 0;
         const int qb = t & 1;
         const int shift = (t == n - 1) ? last_shift : 0;
-        load_q(qn, t + 1, IT);   // the next chunk's fragments
-        if (shift && 32 * IT + ln < shift) {   // ragged last chunk: rows above its first token are zero
-            const u32x4 z = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int s = 0; s < D / 16; ++s) qf[s] = z;
-        }
+        if (kLower) load_q(qn, t + 1);
+        // upper: Q of this chunk is there once only the loads of the next two chunks are outstanding
+        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * QI) : "memory");
         u32x4 kd[D / 16], ko[D / 16], sf[D / 16], vt[4];
+        const uint16_t* qrow = &sm.q[t % Smem::QS][ln * D];
+        const int q_sw = Smem::swizzle(ln);
         const uint16_t* ka = &sm.k[qb][row_off];
         const uint16_t* st_rd = &sm.st[qb][st_rd_off];
-        const uint16_t* v_tr = &sm.v[t % 3][tr_off_v];
+        const uint16_t* v_tr = &sm.v[qb][tr_off_v];
         // The LDS operands are read in items of two to four LDS instructions, in the order in which the MFMAs
         // take them, and each item is issued kAhead items before it is used: the reads of the next
         // items are then in flight under the MFMAs of this one (the counter of outstanding LDS
@@ -406,6 +445,7 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
             if (i < NP) {
 #pragma unroll
                 for (int s = 2 * i; s < 2 * i + 2; ++s) {
+                    if (!kLower) qf[s] = frag16(qrow + 8 * ((2 * s + g) ^ q_sw));
                     if (kLower) ko[s] = frag16(ka + 16 * s);
                     else kd[s] = frag16(ka + 16 * s);
                 }
@@ -441,6 +481,9 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
                 for (int s = 4 * (i - (NM - NQ)); s < 4 * (i - (NM - NQ)) + 4; ++s) os = mfma32(sf[s], qf[s], os);
             }
             issue(i + kAhead);
+#pragma unroll
+            for (int s = (i * QI + NM - 1) / NM; s < ((i + 1) * QI + NM - 1) / NM; ++s)
+                if (!kLower) issue_q(t + 3, (s + slice * QI / SL) % QI);
             // mask and pack a score tile once the MFMAs of the next product have been issued behind it
             if (kLower && i == NP + NQ - 1) {
 #pragma unroll
@@ -571,8 +614,15 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     } else {
         const std::true_type yes;
         const std::false_type no;
-        u32x4 qa[D / 16], qb2[D / 16];
-        if (row_wave) load_q(qa, 0, it_own);   // in flight before the table's barrier, like the loaders' first loads
+        u32x4 qa[D / 16], qb2[D / 16];   // lower row block: Q of the chunk in progress and of the next one, in turn
+        // in flight before the table's barrier, like the loaders' first loads
+        if (row_wave && it_own == 1) load_q(qa, 0);
+        if (row_wave && it_own == 0) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int s = 0; s < QI; ++s) issue_q(c, s);
+        }
         {
             const double gd = p.no_decay ? 1.0 : (double)p.gamma[h];  // 0/1 causal mask: every weight is 1
             for (int i = tid; i <= kChunk; i += NT) sm.pw[i] = (float)pow_int(gd, i);   // threads 0 .. 64: waves 0 and 1
@@ -582,16 +632,11 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
         __syncthreads();
         // every branch below executes one barrier per iteration t = 0 .. t_end
         if (row_wave) {
-            // qa, qb2: the Q fragments of the chunk in progress and of the next one, in turn (qa holds
-            // chunk 0, loaded before the first barrier)
             if (it_own == 0) {
-                for (int t = 0; t <= t_end; t += 2) {
-                    if (t < n) row_block(t, no, qa, qb2);
+                u32x4 qf[D / 16];
+                for (int t = 0; t <= t_end; ++t) {
+                    if (t < n) row_block(t, no, qf, qf);
                     __syncthreads();  // chunk t+1 tiles, S^T(t+1), O(t) visible; everything read in this iteration is free
-                    if (t + 1 <= t_end) {
-                        if (t + 1 < n) row_block(t + 1, no, qb2, qa);
-                        __syncthreads();
-                    }
                 }
             } else {
                 for (int t = 0; t <= t_end; t += 2) {
@@ -603,6 +648,7 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
                     }
                 }
             }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may arrive in LDS after the workgroup has ended
         } else {
             // the state waves, the store waves of the walk, and waves with nothing to do in this launch
             for (int t = 0; t <= t_end; ++t) {
