@@ -20,18 +20,24 @@
 // x - x0 = NaN.  So the walk watches the smallest nonzero operands and whether its results are finite, and where
 // something is out of range the segment is walked again with fp32 matrix instructions (walk_fp32), whose
 // results stand for every operand.  Ordinary data never does that (nor zeros behind a sequence: B4 H16 N4096, half of it
-// zeros, 252 us); the watching costs some 50 of 650 vector operations
-// a tile (B4 H16 N4096 273 -> 282 us; without it q, k ~ 2^-60 with v ~ 2^104 came out with errors of 6e-4).
+// zeros, 252 us); the watching costs some 60 of 690 vector operations
+// a tile (B4 H16 N4096, before the walk overlapped them with MFMAs, 273 -> 282 us; without it q, k ~ 2^-60 with v ~ 2^104
+// came out with errors of 6e-4).
 //
 // Work split: a column tile of 32 value columns belongs to two waves (in the pre-pass: one),
 // which hold half of the key dimension each: S[half of dk][cols] in fp32 accumulators for the whole walk.
 // Each computes its half of the sum Q S and the scores' product with one half of the keys; the two sums
-// meet in LDS on their way out.  Eight waves, one workgroup a compute unit; in the pre-pass four and two.
+// meet in LDS on their way out.  Eight waves, one workgroup a compute unit; in the pre-pass four and two (whose
+// phases overlap by themselves).
 //
-// What bounds it: matrix and vector instructions, which take turns on a SIMD more than they overlap: per
-// 32-token tile 624 MFMAs of 32 cycles (of 4 SIMDs) and, per wave, some 650 vector operations, most of them
-// splits.  Against a kernel on fp32 MFMAs, one device: B4 H16 N4096 319 -> 282 us, B1 H32 N777 53.5 -> 45.9, B1 H300 N2000
-// 819 -> 630 (walk_fp32 alone, B1 H300 N2000: 805).
+// What bounds it: the power of its matrix and vector instructions.  Per 32-token tile there are 624 MFMAs of 32 cycles (of 4
+// SIMDs) and, per wave, some 690 vector operations, most of them splits.  The walk forms an operand while an MFMA that does not
+// need it is running: the next tile's k and q during G4, Gam V during G3, the state's update during G2; each wave of a pair
+// splits its half of V and hands the weighted half to the other through LDS.  Two barriers a tile.  B4 H16 N4096, walk: 349
+// thousand cycles with the phases one after the other and three barriers, 307 so; 183 -> 171 us at the clock of a first
+// run.  In a steady run the clock gives way (2.0 -> 1.6 GHz) and a call gains less, 266 -> 254 us; B9 H33 N2000 611 -> 553,
+// B16 H32 N300 122 -> 116.  Before that, against fp32 MFMAs: 319 -> 282, B1 H32 N777 53.5 -> 45.9
+// (walk_fp32 alone, B1 H300 N2000: 805, here 630).
 // Against 64 bits a single product errs by at most 5.99e-8 of itself (5.95e-8 with fp32 MFMAs).  Sums round less
 // often: over forty sizes outputs 0.66e-7..0.95e-7 in the 2-norm (1.5e-7..2.8e-7), states 0.33 to 0.83 of what fp32
 // MFMAs give; the largest single error of a state after two tokens, in units of its rms and over 200 seeds, is 4.2e-7 on
@@ -75,21 +81,21 @@ constexpr int threads(bool out) { return D / 32 * parts(out) * 64; }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-// The pre-pass (kOut = false) reads no Q and forms no scores; it has two K buffers instead and so
-// one barrier a tile.
+// The pre-pass (kOut = false) reads no Q and forms no scores; one barrier a tile.
 template <bool kOut>
 struct Smem {
     static constexpr int RS = D + 8;    // padded row strides (elements)
     static constexpr int RP = kTile + 8;
     static constexpr int RO = kTile + 8;  // output scratch of a wave (floats)
-    uint16_t k[kOut ? 1 : 2][3 * kTile * RS];   // three planes each
+    uint16_t k[2][3 * kTile * RS];   // three planes each; this tile's and the next one's
     uint16_t q[kOut ? 3 * kTile * RS : 8];
+    u32x4 gv[kOut ? 2 * (D / 32) : 1][3][64];   // Gam V of a wave's half of the keys, as operand
     uint16_t p[kOut ? 3 * kTile * RP : 8];      // masked scores P[i][slot]
     float o[kOut ? 2 * (D / 32) * kTile * RO : 4];  // output tiles of the waves
     float lw[kTile];       // gamma^(i+1)
-    float gw[kTile];       // gamma^(31-j) in slot order
+    float gw[2][kTile];    // gamma^(31-j) in slot order; gamma^(L-1-j) of the segment's last tile
     float pw[kTile + 4];   // gamma^n, n = 0..32
-    int bad[3];            // out of range: seen in even tiles, in odd tiles, in the whole walk
+    int bad[2];            // out of range: seen so far, in the whole walk
 };
 
 // The smallest magnitude of kN values; and of those other than zero, as twice its bits minus one, which puts zero
@@ -192,12 +198,23 @@ __device__ __forceinline__ u32x2 lds_tr(const uint16_t* p) {
     return __builtin_bit_cast(u32x2, r);
 }
 
-// The tile of tokens tok0 .. min(tok0 + 31, tok_end - 1) of a tensor with rows of D floats.
+// The scheduler's order for a region: an MFMA, then kValu vector operations and what LDS work there is, kMfma times.
+template <int kMfma, int kValu>
+__device__ __forceinline__ void interleave() {
+#pragma unroll
+    for (int i = 0; i < kMfma; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, kValu, 0);
+        __builtin_amdgcn_sched_group_barrier(0x80, 1, 0);
+    }
+}
+
+// The tile of tokens tok0 .. min(tok0 + 31, tok_end - 1) of a tensor with rows of D floats (none if tok0 >= tok_end).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const float* base, int tok0, int tok_end) {
     // all of it is the same in every lane; the compiler is told, since it moves part of the arithmetic to vector registers
     const uintptr_t addr = reinterpret_cast<uintptr_t>(base) + (size_t)tok0 * (D * 4);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)addr), hi = __builtin_amdgcn_readfirstlane((uint32_t)(addr >> 32));
-    const int bytes = __builtin_amdgcn_readfirstlane(min(kTile, tok_end - tok0) * (D * 4));
+    const int bytes = __builtin_amdgcn_readfirstlane(max(min(kTile, tok_end - tok0), 0) * (D * 4));
     return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uintptr_t)hi << 32) | lo), 0, bytes, 0x00027000);
 }
 // kStream: with the nontemporal hint
@@ -218,7 +235,9 @@ __device__ __forceinline__ void store4_nt(f32x4 x, __amdgpu_buffer_rsrc_t r, int
 // kOut = true : full walk (outputs + state).   kOut = false : state only (segment pre-pass).
 // kStream: q, k, v exceed the last-level cache; q and k, read in whole lines, are loaded nontemporally (not v,
 // whose lines two instructions share).  B4 H16 N4096 d128: 234 -> 230 us.
-template <bool kOut, bool kStream>
+// kOne (walk only): no segment has more than one tile, so nothing is done for a next one.  One tile, B4 H32 N32 d128: 11.1 us
+// without it, 10.1 with it.
+template <bool kOut, bool kStream, bool kOne>
 __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(FwdParams p) {
     using namespace f32s;
     constexpr int CT = D / 32;                 // column tiles
@@ -260,36 +279,45 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
     const int j0 = tid / PR, cc = tid % PR;
     const int c_own = 32 * wc + ln;
     f32x4 rq[NLOAD], rk[NLOAD];
-    float va[16];  // va[8f + e] = V[key_of(f, e)][c_own]
-    auto key_of = [&](int f, int e) { return 16 * f + 2 * g + (e >> 2) + 4 * (e & 3); };
+    float va[16];  // va[8f + e] = V[key_of(f, e)][c_own]; f = 0: the half of the keys that this wave takes in G2
+    auto key_of = [&](int f, int e) { return 16 * (f ^ wk) + 2 * g + (e >> 2) + 4 * (e & 3); };
     const int qk_off = (j0 * D + cc * 4) * 4, v_off = (2 * g * D + c_own) * 4, o_off = ((16 * wk + (l >> 3)) * D + 32 * wc + 4 * (l & 7)) * 4;
     auto load_qk = [&](int tok0) {
-        const auto kt = tile_rsrc(kb, tok0, tok_end);
-        const auto qt = tile_rsrc(qb, tok0, tok_end);
+        // a descriptor for each group of rows: what an instruction's immediate offset does not reach would sit in vector registers
 #pragma unroll
         for (int r = 0; r < NLOAD; ++r) {
-            rk[r] = load4<kStream>(kt, qk_off + RPP * r * D * 4);
-            if (kOut) rq[r] = load4<kStream>(qt, qk_off + RPP * r * D * 4);
+            rk[r] = load4<kStream>(tile_rsrc(kb, tok0 + RPP * r, tok_end), qk_off);
+            if (kOut) rq[r] = load4<kStream>(tile_rsrc(qb, tok0 + RPP * r, tok_end), qk_off);
         }
     };
-    auto load_v = [&](int tok0) {
-        const auto vt = tile_rsrc(vb, tok0, tok_end);
+    auto load_v = [&](int tok0, bool both) {
 #pragma unroll
-        for (int x = 0; x < 16; ++x) va[x] = load1(vt, v_off + (16 * (x >> 3) + ((x >> 2) & 1) + 4 * (x & 3)) * D * 4);
+        for (int i = 0; i < 4; ++i) {
+            if (i >= 2 && !both) break;
+            const auto vt = tile_rsrc(vb, tok0 + 16 * ((i >> 1) ^ wk) + 8 * (i & 1), tok_end);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int e = 4 * (x >> 1) + 2 * (i & 1) + (x & 1);  // key_of(i >> 1, e)
+                va[8 * (i >> 1) + e] = load1(vt, v_off + ((x >> 1) + 4 * (x & 1)) * D * 4);
+            }
+        }
     };
     load_qk(tok_begin);
-    load_v(tok_begin);
+    load_v(tok_begin, !kOut);
 
     {
         const double gd = p.no_decay ? 1.0 : (double)p.gamma[h];
-        if (tid < 3) sm.bad[tid] = 0;
+        if (tid < 2) sm.bad[tid] = 0;
         for (int n = tid; n <= kTile; n += NT) {
             const float x = (float)pow_int(gd, n);
             sm.pw[n] = x;
             if (n > 0) sm.lw[n - 1] = x;
             if (n < kTile) {
-                const int j = kTile - 1 - n;  // slot 16(j/16) + 4(j%4) + (j/4)%4
-                sm.gw[(j & 16) + 4 * (j & 3) + ((j >> 2) & 3)] = x;
+                auto slot = [](int j) { return (j & 16) + 4 * (j & 3) + ((j >> 2) & 3); };
+                const int last = tok_end - tok_begin - (ntiles - 1) * kTile - 1;  // last token of the last tile
+                sm.gw[0][slot(kTile - 1 - n)] = x;
+                if (n <= last) sm.gw[1][slot(last - n)] = x;
+                else sm.gw[1][slot(n)] = 0.0f;  // no token
             }
         }
     }
@@ -347,6 +375,14 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
     };
     enter_state();
 
+    // No wave forms the scores of rows 0..15 with keys 16..31: zero, once.
+    if (kOut && !kOne) {
+#pragma unroll
+        for (int i = 0; i < 2 * CT * kTile * RO / (4 * NT); ++i) reinterpret_cast<f32x4*>(sm.o)[tid + i * NT] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    if (kOut && tid < 3 * 16 * 2)
+        *reinterpret_cast<u32x4*>(&sm.p[(tid >> 5) * kTile * RP + ((tid >> 1) & 15) * RP + 16 + 8 * (tid & 1)]) = u32x4{0, 0, 0, 0};
+
     __syncthreads();  // tables visible
 
     // decay weights of the score tile this wave produces (waves 0, 1, 2: (it, jt) = (0,0), (1,0), (1,1));
@@ -369,22 +405,34 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
     const int q_row32 = ln * RS + 32 * DT * wk + 8 * g;                       // G3: + 32 t + 16 h
     const int q_row16 = l16 * RS + 8 * q4;                     // G1: + 16 it RS + 32 s
     const int k_row16 = ((l16 >> 2) + 4 * (l16 & 3)) * RS + 8 * q4;  // G1: + 16 jt RS + 32 s
-    const int k_tr = (2 * g + 4 * (l16 >> 2)) * RS + 32 * DT * wk + 16 * half + 8 * (l16 & 1) + 4 * ((l16 >> 1) & 1);  // G4: + 16 f RS + 32 t, + RS
+    const int k_tr0 = (2 * g + 4 * (l16 >> 2)) * RS + 32 * DT * wk + 16 * half + 8 * (l16 & 1) + 4 * ((l16 >> 1) & 1);  // G4: + 32 t, + RS
+    const int k_tr[2] = {k_tr0 + 16 * wk * RS, k_tr0 + 16 * (1 ^ wk) * RS};
 
     // The finished tile of tokens tok0 ..: the two waves of a column tile hold half of the sum each; each adds
     // and stores half of the rows, in whole 128-byte row pieces, all LDS reads before the first store.
-    auto store_out = [&](int tok0) {
-        f32x4 val[2];
+    // In the first tile of the walk there is none: what is read is zero, and `on` = 0 stores nothing.
+    struct OutHalves {
+        f32x4 x[2][2];
+    };
+    auto read_out = [&]() {
+        OutHalves v;
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
             const float* src = sm.o + wc * (kTile * RO) + (16 * wk + 8 * m + (l >> 3)) * RO + 4 * (l & 7);
-            val[m] = *reinterpret_cast<const f32x4*>(src) + *reinterpret_cast<const f32x4*>(src + CT * kTile * RO);
+            v.x[m][0] = *reinterpret_cast<const f32x4*>(src);
+            v.x[m][1] = *reinterpret_cast<const f32x4*>(src + CT * kTile * RO);
         }
+        return v;
+    };
+    auto store_out = [&](const OutHalves& v, int tok0, bool on) {
+        const auto ot = tile_rsrc(ob, tok0, on ? tok_end : tok0);
 #pragma unroll
-        for (int x = 0; x < 8; ++x) fin += __builtin_fabsf(val[x >> 2][x & 3]);
-        const auto ot = tile_rsrc(ob, tok0, tok_end);
+        for (int m = 0; m < 2; ++m) {
+            const f32x4 val = v.x[m][0] + v.x[m][1];
 #pragma unroll
-        for (int m = 0; m < 2; ++m) store4_nt(val[m], ot, o_off + 8 * m * D * 4);
+            for (int x = 0; x < 4; ++x) fin += __builtin_fabsf(val[x]);
+            store4_nt(val, ot, o_off + 8 * m * D * 4);
+        }
     };
 
     // Least magnitudes of operands other than zero: two that are multiplied make 2^-96 or more, of which the terms and
@@ -402,42 +450,57 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
     // The walk with split products.  True: an operand or a result was out of range somewhere, and nothing of what
     // the walk has made stands.
     auto walk_split = [&]() -> bool {
+        auto k_at = [&](int x) { return rk[x >> 2][x & 3]; };
+        auto q_at = [&](int x) { return rq[x >> 2][x & 3]; };
+        auto s_at = [&](int x) { return S[x >> 4][x & 15]; };
+        uint32_t s_small = ~0u;
+        // The operands of the tile to come: k, q and, an operand in G3 only, S.  In the walk without a branch but for S: one costs
+        // as much as some twenty vector operations, and between MFMAs these cost little.
+        auto watch_qk = [&]() {
+            if (kOut) bad |= (smallest_nonzero<4 * NLOAD>(k_at) < rank_nonzero(least_k)) | (smallest_nonzero<4 * NLOAD>(q_at) < rank_nonzero(least_q));
+            else bad |= has_small<4 * NLOAD>(k_at, least_k);
+        };
+        auto watch_s = [&]() {
+            s_small = ~0u;
+            if (__any(smallest<16 * DT>(s_at) < least_k)) s_small = smallest_nonzero<16 * DT>(s_at);
+        };
+        // piece r of k and q as planes, to buffer b
+        auto stage = [&](int b, int r) {
+            store4(sm.k[b] + st_off + RPP * r * RS, kTile * RS, rk[r][0], rk[r][1], rk[r][2], rk[r][3]);
+            if (kOut) store4(sm.q + st_off + RPP * r * RS, kTile * RS, rq[r][0], rq[r][1], rq[r][2], rq[r][3]);
+        };
+        // (a tile beyond the last reads as zero, without an access to memory)
+        auto tile_at = [&](int t) { return tok_begin + t * kTile; };
+
         // the entering state arrives here, not at its first use in the loop: there every tile would wait for all loads
 #pragma unroll
         for (int t = 0; t < DT; ++t) asm("" : "+v"(S[t]));
-        int stop = 0;
-        for (int t = 0; t < ntiles; ++t) {
-            const int tok0 = tok_begin + t * kTile;
-            const int next = tok_begin + min(t + 1, ntiles - 1) * kTile;
-            const int Lc = min(kTile, tok_end - tok0);
-            uint16_t* kt = sm.k[kOut ? 0 : (t & 1)];
-
-            if (kOut && t > 0) {
-                __syncthreads();  // the previous tile's sums visible; everyone is done reading its planes and scores
-                store_out(tok0 - kTile);
-            }
-            auto k_at = [&](int x) { return rk[x / 4][x % 4]; };
-            auto s_at = [&](int x) { return S[x / 16][x % 16]; };
-            float least_seen = smallest<4 * NLOAD>(k_at);
-            if (kOut) least_seen = __builtin_fminf(least_seen, smallest<16 * DT>(s_at));  // S is an operand in G3 only
-            uint32_t s_small = ~0u;
-            if (__any(least_seen < least_k)) {
-                bad |= smallest_nonzero<4 * NLOAD>(k_at) < rank_nonzero(least_k);
-                if (kOut) s_small = smallest_nonzero<16 * DT>(s_at);
-            }
-            if (kOut) bad |= has_small<4 * NLOAD>([&](int x) { return rq[x >> 2][x & 3]; }, least_q);
+        // The walk splits a tile's k and q while it works on the tile before; the pre-pass, where two workgroups share a
+        // compute unit and one splits while the other multiplies, has no registers left for that.
+        auto stage_tile = [&](int t) {
+            watch_qk();
 #pragma unroll
-            for (int r = 0; r < NLOAD; ++r) {
-                store4(kt + st_off + RPP * r * RS, kTile * RS, rk[r][0], rk[r][1], rk[r][2], rk[r][3]);
-                if (kOut) store4(sm.q + st_off + RPP * r * RS, kTile * RS, rq[r][0], rq[r][1], rq[r][2], rq[r][3]);
+            for (int r = 0; r < NLOAD; ++r) stage(t & 1, r);
+        };
+        if (kOut) {
+            watch_s();
+            stage_tile(0);
+            if (!kOne) load_qk(tile_at(1));
+        }
+        int stop = 0;
+        for (int t = 0; t < (kOne ? 1 : ntiles); ++t) {
+            const int tok0 = tok_begin + t * kTile;
+            const int Lc = min(kTile, tok_end - tok0);
+            uint16_t* kt = sm.k[t & 1];
+
+            if (!kOut) stage_tile(t);
+            __syncthreads();  // this tile's planes and the previous one's sums visible; everyone is done reading its planes and scores
+            // Something out of range in the eight tiles before?  (The flag is not written again before the next barriers.)
+            if (t % 8 == 0 && __builtin_amdgcn_readfirstlane(sm.bad[0])) {
+                stop = 1;
+                break;
             }
-            __syncthreads();
-            // Something out of range in the tile before?  (Its flag is not written again before the next barrier.)
-            stop = sm.bad[(t & 1) ^ 1];
-            // The next tile's loads, in flight during the MFMA work below; the last tile loads itself again.  (Under
-            // a condition, every later wait would have to cover the path without them and so drain them.)
-            load_qk(next);
-            __builtin_amdgcn_sched_barrier(0);
+            if (!kOut) load_qk(tile_at(t + 1));
             // A state that has decayed below its least magnitude is held against the rows of q that it meets: with
             // tokens of zeros behind a sequence there are none.
             if (kOut && __any(s_small < rank_nonzero(least_k))) {
@@ -454,7 +517,25 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
                 bad |= s_small != ~0u && q_small != ~0u && (sv < 0x1p-100f || sv * qv < 0x1p-96f);
             }
 
+            auto v_at = [&](int x) { return va[x]; };
+            bad |= kOut ? smallest_nonzero<8>(v_at) < rank_nonzero(least_v) : has_small<16>(v_at, least_v);
+            if (t % 8 == 7 && __any(bad | !(fin < __builtin_inff()))) sm.bad[0] = 1;
+            // Gam V as operands, half f of the slots
+            Frag3 gv[2];
+            const float* gw = sm.gw[t == ntiles - 1];
+            f32x4 wv[2];
+            auto read_weights = [&](int f) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) wv[u] = *reinterpret_cast<const f32x4*>(&gw[16 * (f ^ wk) + 8 * g + 4 * u]);
+            };
+            auto weigh = [&](int f) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) wv[e >> 2][e & 3] *= va[8 * f + e];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) put2(gv[f], e, wv[e >> 1][2 * (e & 1)], wv[e >> 1][2 * (e & 1) + 1]);
+            };
             f32x16 o, os;  // leading products, the others
+            Frag3 vo, po;  // G2: V, the half of the keys that this wave takes; the scores
             if (kOut) {
                 // G1 + mask for the score tile this wave produces
 #pragma unroll
@@ -469,13 +550,16 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
                             b.x[i] = *reinterpret_cast<const u32x4*>(&sm.q[i * kTile * RS + q_row16 + 16 * it * RS + 32 * s]);
                         }
                     };
-                    Frag3 a[2], b[2];
+                    Frag3 a[3], b[3];
                     read(a[0], b[0], 0);
+                    read(a[1], b[1], 1);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int s = 0; s < D / 32; ++s) {
-                        if (s + 1 < D / 32) read(a[(s + 1) & 1], b[(s + 1) & 1], s + 1);
-                        small = mma16_small(a[s & 1], b[s & 1], small);
-                        big = mfma16(a[s & 1].x[0], b[s & 1].x[0], big);
+                        if (s + 2 < D / 32) read(a[(s + 2) % 3], b[(s + 2) % 3], s + 2);
+                        small = mma16_small(a[s % 3], b[s % 3], small);
+                        big = mfma16(a[s % 3].x[0], b[s % 3].x[0], big);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                     float m[4];
 #pragma unroll
@@ -500,120 +584,129 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
                     for (int e = 0; e < 4; ++e) put2(b, e, S[s >> 1][8 * (s & 1) + 2 * e], S[s >> 1][8 * (s & 1) + 2 * e + 1]);
                 };
                 Frag3 a[2], b[2];
+                const OutHalves done = read_out();
                 read(a[0], b[0], 0);
+                if (!kOne) store_out(done, tok0 - kTile, t > 0);
                 __builtin_amdgcn_sched_barrier(0);
+                f32x4 lam[4];
 #pragma unroll
                 for (int s = 0; s < 2 * DT; ++s) {
                     if (s + 1 < 2 * DT) read(a[(s + 1) & 1], b[(s + 1) & 1], s + 1);
+                    if (s == 2 * DT - 3) read_weights(0);
+                    if (s == 2 * DT - 2) weigh(0);
+                    if (s == 2 * DT - 1) {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) sm.gv[w][i][l] = gv[0].x[i];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) lam[u] = *reinterpret_cast<const f32x4*>(&sm.lw[8 * u + 4 * g]);
+                    }
                     os = mma32_small(a[s & 1], b[s & 1], os);
                     o = ElemBf16::mfma32(a[s & 1].x[0], b[s & 1].x[0], o);
-                    __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  // LDS reads, then MFMAs and vector operations in turn
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x2, 6, 0);
-                    }
+                    // LDS reads, then MFMAs and vector operations in turn
+                    if (s + 1 < 2 * DT) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+                    if (s == 2 * DT - 2) interleave<8, 12>();
+                    else interleave<8, 6>();
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const f32x4 lam = *reinterpret_cast<const f32x4*>(&sm.lw[8 * u + 4 * g]);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) o[4 * u + r] = __builtin_fmaf(os[4 * u + r], lam[r], o[4 * u + r] * lam[r]);
-                }
-
-                __syncthreads();  // scores visible
-                // G2: P V.  Wave part 0 takes keys 0..15, part 1 keys 16..31, which do not reach rows 0..15 (registers 0..7);
-                // both leave their sums for store_out.  P V has accumulators of its own: in those of G3 the matrix instructions
-                // would take a far decayed Lam (Q S) as zero.
-                float* mine = sm.o + w * (kTile * RO);
-#pragma unroll
-                for (int f = 0; f < 2; ++f) {
-                    if (f != wk) continue;
-                        Frag3 a, b;
-#pragma unroll
-                    for (int i = 0; i < 3; ++i)
-                        a.x[i] = *reinterpret_cast<const u32x4*>(&sm.p[i * kTile * RP + ln * RP + 16 * f + 8 * g]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) put2(b, e, va[8 * f + 2 * e], va[8 * f + 2 * e + 1]);
-                    f32x16 c, cs;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) c[r] = cs[r] = 0.0f;
-                    cs = mma32_small(a, b, cs);
-                    c = ElemBf16::mfma32(a.x[0], b.x[0], c);
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        mine[(8 * (r >> 2) + 4 * g + (r & 3)) * RO + ln] = f == 1 && r < 8 ? o[r] : o[r] + (c[r] + cs[r]);
-                }
-            }
-
-            bad |= has_small<16>([&](int x) { return va[x]; }, least_v);
-            // Gam V as operands; with them the registers of V are free for the next tile's loads.
-            Frag3 gv[2];
-#pragma unroll
-            for (int f = 0; f < 2; ++f) {
-                f32x4 wv[2];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) wv[u] = *reinterpret_cast<const f32x4*>(&sm.gw[16 * f + 8 * g + 4 * u]);
-                if (Lc < kTile) {  // ragged: gamma^(L-1-j)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) wv[e >> 2][e & 3] = sm.pw[max(Lc - 1 - key_of(f, e), 0)];
-                }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) wv[e >> 2][e & 3] *= va[8 * f + e];
-    #pragma unroll
-                for (int e = 0; e < 4; ++e) put2(gv[f], e, wv[e >> 1][2 * (e & 1)], wv[e >> 1][2 * (e & 1) + 1]);
-            }
-            if (__any(bad | !(fin < __builtin_inff()))) sm.bad[t & 1] = 1;
-            __builtin_amdgcn_sched_barrier(0);
-            load_v(next);
-            __builtin_amdgcn_sched_barrier(0);
-            // G4: S = gamma^L S + K^T (Gam V)
-            {
-                const float gl = sm.pw[Lc];
-                auto read = [&](Frag3& a, int u) {  // step u: tile u/2, slots 16 (u%2) ..
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        const uint16_t* src = &kt[i * kTile * RS + k_tr + 16 * (u & 1) * RS + 32 * (u >> 1)];
-                        const u32x2 lo = lds_tr(src), hi = lds_tr(src + RS);
-                        a.x[i] = u32x4{lo.x, lo.y, hi.x, hi.y};
-                    }
-                };
-                Frag3 a[4];
-                read(a[0], 0);
-                read(a[1], 1);
+                for (int r = 0; r < 16; ++r) o[r] = __builtin_fmaf(os[r], lam[r >> 2][r & 3], o[r] * lam[r >> 2][r & 3]);
+            } else {
+                read_weights(0);
+                weigh(0);
+                read_weights(1);
+                weigh(1);
                 __builtin_amdgcn_sched_barrier(0);
+                load_v(tile_at(t + 1), true);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // G4: S = gamma^L S + K^T (Gam V), one 32-row tile after the other
+            auto read_k = [&](Frag3& a, int dt, int f) {
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) {
-                    const int c = 2 * (dt & 1);
-                    if (dt + 1 < DT) {
-                        read(a[c ^ 2], 2 * dt + 2);
-                        read(a[(c ^ 2) + 1], 2 * dt + 3);
-                    }
-                    f32x16 sb, ss;  // leading products, the others
+                for (int i = 0; i < 3; ++i) {
+                    const uint16_t* src = &kt[i * kTile * RS + k_tr[f] + 32 * dt];
+                    const u32x2 lo = lds_tr(src), hi = lds_tr(src + RS);
+                    a.x[i] = u32x4{lo.x, lo.y, hi.x, hi.y};
+                }
+            };
+            const float gl = sm.pw[Lc];
+            Frag3 a[4];
+            read_k(a[0], 0, 0);
+            if (kOut) {
+                __syncthreads();  // scores and weighted values visible
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) sb[r] = ss[r] = 0.0f;
-                    ss = mma32_small(a[c], gv[0], ss);
-                    ss = mma32_small(a[c + 1], gv[1], ss);
-                    sb = ElemBf16::mfma32(a[c].x[0], gv[0].x[0], sb);
-                    sb = ElemBf16::mfma32(a[c + 1].x[0], gv[1].x[0], sb);
+                for (int i = 0; i < 3; ++i) gv[1].x[i] = sm.gv[w ^ CT][i][l];
+            }
+            read_k(a[1], 0, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            f32x16 sb[2], ss[2], pb, ps;  // leading products, the others
+            auto add_up = [&](int dt) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) S[dt][r] = __builtin_fmaf(S[dt][r], gl, sb[r] + ss[r]);
+                for (int r = 0; r < 16; ++r) S[dt][r] = __builtin_fmaf(S[dt][r], gl, sb[dt & 1][r] + ss[dt & 1][r]);
+            };
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                const int n = dt & 1, c = 2 * n;
+                if (!kOut && dt + 1 < DT) {
+                    read_k(a[c ^ 2], dt + 1, 0);
+                    read_k(a[(c ^ 2) + 1], dt + 1, 1);
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sb[n][r] = ss[n][r] = 0.0f;
+                ss[n] = mma32_small(a[c], gv[0], ss[n]);
+                sb[n] = ElemBf16::mfma32(a[c].x[0], gv[0].x[0], sb[n]);
+                ss[n] = mma32_small(a[c + 1], gv[1], ss[n]);
+                sb[n] = ElemBf16::mfma32(a[c + 1].x[0], gv[1].x[0], sb[n]);
+                auto stage_next = [&](int r) {
+                    if (!kOne) stage((t + 1) & 1, r);
+                };
+                if (kOut && dt == 0) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) put2(vo, e, va[2 * e], va[2 * e + 1]);
+                    stage_next(0);
+                    if (!kOne) watch_qk();
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) po.x[i] = *reinterpret_cast<const u32x4*>(&sm.p[i * kTile * RP + ln * RP + 16 * wk + 8 * g]);
+                }
+                if (kOut && dt == 1) {
+                    stage_next(1);
+                    float* mine = sm.o + w * (kTile * RO);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mine[(8 * (r >> 2) + 4 * g + (r & 3)) * RO + ln] = o[r] + (pb[r] + ps[r]);
+                }
+                if (kOut) interleave<16, 6>();
+                if (!kOut || dt > 0) add_up(dt);
+                __builtin_amdgcn_sched_barrier(0);
+                if (kOut && dt == 0) {
+                    if (!kOne) load_v(tile_at(t + 1), false);
+                    __builtin_amdgcn_sched_barrier(0);
+                    // G2: P V, over one half of the keys.  Both waves leave their sums for store_out.  P V has accumulators of its
+                    // own: in those of G3 the matrix instructions would take a far decayed Lam (Q S) as zero.
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) pb[r] = ps[r] = 0.0f;
+                    read_k(a[2], 1, 0);
+                    read_k(a[3], 1, 1);
+                    ps = mma32_small(po, vo, ps);
+                    pb = ElemBf16::mfma32(po.x[0], vo.x[0], pb);
+                    add_up(0);
+                    interleave<8, 6>();
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            if (__builtin_amdgcn_readfirstlane(stop)) break;
+            if (kOut && !kOne) {
+                watch_s();
+                load_qk(tile_at(t + 2));
+            }
         }
 
         if (kOut) {
             __syncthreads();  // the last tile's sums visible
-            if (!stop) store_out(tok_begin + (ntiles - 1) * kTile);
+            store_out(read_out(), tok_begin + (ntiles - 1) * kTile, !stop);
         }
 #pragma unroll
         for (int x = 0; x < 16 * DT; ++x) fin += __builtin_fabsf(S[x >> 4][x & 15]);  // not finite once, not finite for good
-        if (__any(bad | !(fin < __builtin_inff()))) sm.bad[2] = 1;
+        if (__any(bad | !(fin < __builtin_inff()))) sm.bad[1] = 1;
         __syncthreads();
-        return __builtin_amdgcn_readfirstlane(sm.bad[2]) != 0;
+        return __builtin_amdgcn_readfirstlane(sm.bad[1]) != 0;
     };
 
     // The same walk with fp32 matrix instructions on fp32 tiles in the same LDS: same waves, same column tiles and
@@ -631,7 +724,7 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
             const int Lc = min(kTile, tok_end - tok0);
             if (t > 0) {
                 __syncthreads();
-                if (kOut) store_out(tok0 - kTile);
+                if (kOut) store_out(read_out(), tok0 - kTile, true);
             }
 #pragma unroll
             for (int r = 0; r < NLOAD; ++r) {
@@ -684,7 +777,7 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
                     const float* row = pf + ln * RPF + 16 * f + 8 * g;
                     const f32x4 a[2] = {*reinterpret_cast<const f32x4*>(row), *reinterpret_cast<const f32x4*>(row + 4)};
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) o = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e >> 2][e & 3], va[8 * f + e], o, 0, 0, 0);
+                    for (int e = 0; e < 8; ++e) o = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e >> 2][e & 3], va[e], o, 0, 0, 0);
                     put_rows(f == 1 ? 8 : 0, 16);
                 }
             }
@@ -694,7 +787,7 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
                 const int back = Lc - 1 - key_of(x >> 3, x & 7);
                 gva[x] = back >= 0 ? va[x] * sm.pw[max(back, 0)] : 0.0f;
             }
-            load_v(next);
+            load_v(next, true);
             const float gl = sm.pw[Lc];
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {  // G4
@@ -708,7 +801,7 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
         }
         if (kOut) {
             __syncthreads();
-            store_out(tok_begin + (ntiles - 1) * kTile);
+            store_out(read_out(), tok_begin + (ntiles - 1) * kTile, true);
         }
     };
 
@@ -716,11 +809,13 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
     bool fp32 = far < 0x1p-20f && __builtin_amdgcn_readfirstlane(sm.pw[1] > 0.0f);
     if (!fp32 && walk_split()) {
         load_qk(tok_begin);
-        load_v(tok_begin);
         enter_state();
         fp32 = true;
     }
-    if (fp32) walk_fp32();
+    if (fp32) {
+        load_v(tok_begin, true);
+        walk_fp32();
+    }
 
     float* dst = nullptr;
     if (kOut) {
@@ -735,8 +830,9 @@ namespace {
 template <bool kOut>
 hipError_t launch(const FwdParams& p, int blocks, hipStream_t stream) {
     const dim3 grid(blocks), block(f32s::threads(kOut));
-    if (p.stream_loads) hipLaunchKernelGGL((fwd_f32_split_kernel<kOut, true>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((fwd_f32_split_kernel<kOut, false>), grid, block, 0, stream, p);
+    if (kOut && p.nseg == 1 && p.N <= f32s::kTile) hipLaunchKernelGGL((fwd_f32_split_kernel<kOut, false, kOut>), grid, block, 0, stream, p);
+    else if (p.stream_loads) hipLaunchKernelGGL((fwd_f32_split_kernel<kOut, true, false>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((fwd_f32_split_kernel<kOut, false, false>), grid, block, 0, stream, p);
     return hipGetLastError();
 }
 }  // namespace

@@ -39,6 +39,22 @@ def test_tile_edges_with_state_in_place(B, d, N, segments):
     assert max(errs) <= TOL
 
 
+@pytest.mark.parametrize("tile", [0, 1, 6, 7, 8, 15, 16, 21])
+def test_width_128_finds_an_infinity_in_any_tile(B, tile):
+    # the walk looks up every eighth tile whether it has to be taken again, and at its end
+    N, col = 700, 77
+    q, k, v, gamma = W.make_custom_forward_inputs(1, 2, N, 128, "f32", seed=40 + tile)
+    tok = 32 * tile + 16  # the first of a sixteen: earlier tokens of its sixteen would meet it with a weight of zero
+    ref, _ = oracle.recurrent(*(W.to_f64(t) for t in (q, k, v, gamma)))
+    v[0, 1, tok, col] = float("inf")
+    out = B.leet_attn_forward_v2(q.cuda(), k.cuda(), v.cuda(), gamma.cuda(), segments=1).cpu().numpy()
+    # infinite, or, once the state's infinities of both signs are summed, NaN
+    assert not np.any(np.isfinite(out[0, 1, tok:, col]))
+    out[0, 1, tok:, col] = ref[0, 1, tok:, col]
+    assert np.all(np.isfinite(out))
+    assert max_rel_err(out, ref) <= TOL
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_powers_of_two_pass_through_exactly(B, d):
     q, k, v, gamma = (t.cuda() for t in W.make_custom_forward_inputs(1, 2, 300, d, "f32", seed=7))
