@@ -63,6 +63,7 @@
 // Outputs are accumulated transposed (lane = token): Lam is one scalar per lane and a lane
 // stores 16 contiguous bytes.  A ragged last chunk is right-aligned in the tile (rows 64-L..
 // hold the tokens), which keeps every decay weight chunk-independent.
+#include <cstddef>
 #include <type_traits>
 
 #include "leet_common.hpp"
@@ -175,6 +176,7 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     typedef CoopSmem<D, kOut> Smem;
     constexpr int RSQ = Smem::RSQ, RSV = Smem::RSV, RSVS = Smem::RSVS, RST = Smem::RST;
     __shared__ __attribute__((aligned(16))) Smem sm;
+    static_assert(offsetof(Smem, q) + sizeof(sm.q) <= 65536, "loads to LDS take their address from 16 bits of M0");
 
     // Block -> (sequence segment, column slice).  Consecutive block ids go round-robin over
     // the 8 XCDs; the SL slices of one segment take ids that are equal modulo 8, so they share
@@ -412,7 +414,9 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
         const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&sm.q[stage][0] + 1024 * s;
         const int r = RPI * s + l / PR;   // row of the block; rows above a ragged chunk's first token re-read that token
         const unsigned off = (unsigned)(max(r - shift, 0) * D + 8 * ((l % PR) ^ Smem::swizzle(r))) * 2;
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(qc) : "memory");
+        // The compiler looks for no hazards in here: a load to LDS needs one wait state after the write of M0, and five after a
+        // vector instruction wrote its address pair (uniform_ptr's, if the compiler keeps it).  s_mov and s_nop 3 are five.
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(qc) : "memory", "m0");
     };
     // qf: the fragments of this chunk (lower: loaded before, upper: read here); qn: where the lower wave's next ones go
     auto row_block = [&](int t, auto lower, u32x4 (&qf)[D / 16], u32x4 (&qn)[D / 16]) {
