@@ -189,6 +189,10 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     const int bh = group / nseg_launch, seg = group % nseg_launch;
     const int h = bh % p.H;
 
+    // By a scalar load, here: a vector load would return behind the first tiles', and the first barrier waits for the table
+    // made of it.
+    const float gamma_h = p.no_decay ? 1.0f : ((const __attribute__((address_space(4))) float*)(uintptr_t)p.gamma)[h];
+
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, so the role branches are scalar
     const int l = tid & 63, ln = l & 31, g = l >> 5;
@@ -255,8 +259,9 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     // ---- loaders: thread -> pieces.  Q, K: piece m is row m RPL + lt/PR, 16 bytes at column
     // 8 (lt%PR); V slice: piece m is row 32 m + lt/4, 16 bytes at column c0 + 8 (lt%4).
     const int qk_row = lt / PR, qk_cc = lt % PR;
-    // The slices of a sequence run in step and want the same K and Q lines; each begins at another row (Q likewise), so
-    // that they do not ask one L2 channel for one line at one time (both through LDS, B4 H16 N4096 cold: 78.3 -> 76.3 us).
+    // The slices of a sequence run in step and want the same K and Q lines; each begins at another row, so that they do not
+    // ask one L2 channel for one line at one time.  us over cold inputs, none / Q alone / both: B4 H16 N4096 84.9 / 78.7 / 77.4,
+    // N2000 of width 256 40.7 / 37.9 / 37.7, B1 H32 N777 18.6 / 17.4 / 17.1; in cache within 1 % of one another.
     auto piece = [&](int m) { return (m + slice * QPL / SL) % QPL; };
     const int v_row = lt >> 2, v_cc = lt & 3;
     const int qk_loff = qk_row * RSQ + qk_cc * 8;
@@ -394,9 +399,16 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
     // memory into registers, one chunk ahead: no LDS read stands before its first product.  Such a load touches 32 rows of
     // 32 bytes, and in both waves these loads took half of the time of all loads over cold inputs (B4 H16 N4096: 64.6 us
     // with them, 34.9 without Q).  So the upper wave fills stages of a Q tile of its own, by loads of whole rows straight
-    // from global memory to LDS, three chunks ahead, and waits for them by its own count of outstanding loads.
-    // us at B4 H16 N4096 in cache / cold, N2000 of width 256: both in registers 64.2 / 82.5, 32.8 / 40.2; both through LDS
-    // 67.7 / 76.9, 34.8 / 39.4 (its reads and writes add to the busiest unit); the upper one 63.4 / 77.7, 32.9 / 38.5.
+    // from global memory to LDS, two chunks ahead, and waits for them by its own count of outstanding loads.
+    // us at B4 H16 N4096 in cache / cold, N2000 of width 256: both in registers 63.3 / 82.9, 32.8 / 41.5; the upper one
+    // through LDS 63.6 / 77.4, 33.6 / 37.7; both (three chunks ahead, where the upper one alone took 63.4 / 77.7, 32.9 / 38.5)
+    // 67.7 / 76.9, 34.8 / 39.4: its reads and writes add to the busiest unit.
+    // How far ahead: what is issued early stands before the first K and V in the compute unit's queue.  us in cache, B5 H16
+    // N356 (two rounds of workgroups), B1 H32 N512, N777: both in registers 15.1, 9.7, 14.6; three chunks before the table's
+    // barrier 15.7, 10.1, 14.7; two 15.3, 10.0, 14.7; one before and one behind it 15.2, 9.9, 14.6; one in all 15.0, 9.8, 14.7, but
+    // then B4 H16 N4096 cold takes 82 us again.  With gamma by a scalar load and the table made by waves that have nothing
+    // to load, one before and one behind: 15.0, 9.8, 14.3.  (Over cold inputs 17.8, 11.3, 17.1 against 19.1, 12.1, 18.4 with
+    // both in registers.)
     auto load_q = [&](u32x4 (&qn)[D / 16], int c) {   // lower row block
         c = min(c, n - 1);
         const int shift = (c == n - 1) ? last_shift : 0;
@@ -425,8 +437,8 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
         const int qb = t & 1;
         const int shift = (t == n - 1) ? last_shift : 0;
         if (kLower) load_q(qn, t + 1);
-        // upper: Q of this chunk is there once only the loads of the next two chunks are outstanding
-        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * QI) : "memory");
+        // upper: Q of this chunk is there once only the loads of the next chunk are outstanding
+        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(QI) : "memory");
         u32x4 kd[D / 16], ko[D / 16], sf[D / 16], vt[4];
         const uint16_t* qrow = &sm.q[t % Smem::QS][ln * D];
         const int q_sw = Smem::swizzle(ln);
@@ -487,7 +499,7 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
             issue(i + kAhead);
 #pragma unroll
             for (int s = (i * QI + NM - 1) / NM; s < ((i + 1) * QI + NM - 1) / NM; ++s)
-                if (!kLower) issue_q(t + 3, (s + slice * QI / SL) % QI);
+                if (!kLower) issue_q(t + 2, (s + slice * QI / SL) % QI);
             // mask and pack a score tile once the MFMAs of the next product have been issued behind it
             if (kLower && i == NP + NQ - 1) {
 #pragma unroll
@@ -623,15 +635,16 @@ __global__ __launch_bounds__(kCoopThreads) void fwd_16bit_coop_kernel(FwdParams 
         if (row_wave && it_own == 1) load_q(qa, 0);
         if (row_wave && it_own == 0) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int s = 0; s < QI; ++s) issue_q(c, s);
+            for (int s = 0; s < QI; ++s) issue_q(0, s);
         }
-        {
-            const double gd = p.no_decay ? 1.0 : (double)p.gamma[h];  // 0/1 causal mask: every weight is 1
-            for (int i = tid; i <= kChunk; i += NT) sm.pw[i] = (float)pow_int(gd, i);   // threads 0 .. 64: waves 0 and 1
-        }
+        // 0/1 causal mask: every weight is 1.  Waves 4 and 5 have nothing else to do yet.
+        const int i_pw = tid - 256;
+        if (i_pw >= 0 && i_pw <= kChunk) sm.pw[i_pw] = (float)pow_int((double)gamma_h, i_pw);
         __syncthreads();  // tables, S^T(0) visible
+        if (row_wave && it_own == 0) {
+#pragma unroll
+            for (int s = 0; s < QI; ++s) issue_q(1, s);
+        }
         read_tables();
         __syncthreads();
         // every branch below executes one barrier per iteration t = 0 .. t_end

@@ -1,8 +1,8 @@
-"""Wait states that software owes the hardware around inline assembly, where the compiler inserts none: read from the
-assembly that the library's own sources compile to.
+"""What the column-split kernel must keep around its loads to LDS, read from the assembly that its source compiles to.
 
-Before a load that writes LDS (its LDS address is M0): one wait state after a scalar write of M0.  Before any
-vector-memory access: five after a vector instruction wrote a scalar register that it reads."""
+Wait states that software owes the hardware around inline assembly, where the compiler inserts none: one between a
+scalar write of M0 and a load that writes LDS (M0 is its LDS address); five between a vector instruction that writes a
+scalar register and a vector-memory access that reads it."""
 import os
 import re
 import shutil
@@ -59,12 +59,27 @@ def test_the_reading_itself(code, bad):
     assert loads == 1 and len(complaints) == bad
 
 
-@pytest.mark.skipif(shutil.which(build.HIPCC) is None, reason="needs hipcc")
-def test_loads_to_lds_have_their_wait_states(tmp_path):
-    out = str(tmp_path / "coop.s")
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    if shutil.which(build.HIPCC) is None:
+        pytest.skip("needs hipcc")
+    out = str(tmp_path_factory.mktemp("asm") / "coop.s")
     cmd = [build.HIPCC, *build.FLAGS, "--offload-device-only", "-S", SOURCE, "-o", out]
     res = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stderr
-    loads, complaints = missing_wait_states(open(out).read())
+    return open(out).read()
+
+
+def test_loads_to_lds_have_their_wait_states(assembly):
+    loads, complaints = missing_wait_states(assembly)
     assert loads > 0
     assert not complaints, f"{len(complaints)} of {loads} loads: {complaints[:3]}"
+
+
+def test_one_chunk_of_q_at_most_stands_before_the_first_k_and_v(assembly):
+    # a compute unit's loads return in order: what the upper row wave issues before the first barrier delays the first tile
+    kernels = re.findall(r"^(_ZN4leet21fwd_16bit_coop_kernelILi(\d+)E\w*):(.*?)^\.Lfunc_end", assembly, flags=re.S | re.M)
+    walks = [(int(d), body) for _, d, body in kernels if "global_load_lds" in body]
+    assert len(walks) == 12
+    for d, body in walks:
+        assert body.split("s_barrier")[0].count("global_load_lds") <= d // 16
