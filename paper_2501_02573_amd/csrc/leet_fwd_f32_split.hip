@@ -495,8 +495,10 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
 
             if (!kOut) stage_tile(t);
             __syncthreads();  // this tile's planes and the previous one's sums visible; everyone is done reading its planes and scores
-            // Something out of range in the eight tiles before?  (The flag is not written again before the next barriers.)
-            if (t % 8 == 0 && __builtin_amdgcn_readfirstlane(sm.bad[0])) {
+            // Something out of range up to the tile before?  Written in even tiles and read in odd ones: not both between two
+            // barriers, or the waves could disagree.  us, all in range / all out of range, B9 H33 N2000, B16 H32 N300: every tile
+            // 554 / 834, 121 / 161; every second 542 / 825, 117 / 151; every eighth 541 / 882, 117 / 218.
+            if (t % 2 == 1 && __builtin_amdgcn_readfirstlane(sm.bad[0])) {
                 stop = 1;
                 break;
             }
@@ -519,7 +521,7 @@ __global__ __launch_bounds__(f32s::threads(kOut), 2) void fwd_f32_split_kernel(F
 
             auto v_at = [&](int x) { return va[x]; };
             bad |= kOut ? smallest_nonzero<8>(v_at) < rank_nonzero(least_v) : has_small<16>(v_at, least_v);
-            if (t % 8 == 7 && __any(bad | !(fin < __builtin_inff()))) sm.bad[0] = 1;
+            if (t % 2 == 0 && __any(bad | !(fin < __builtin_inff()))) sm.bad[0] = 1;
             // Gam V as operands, half f of the slots
             Frag3 gv[2];
             const float* gw = sm.gw[t == ntiles - 1];

@@ -41,7 +41,7 @@ def test_tile_edges_with_state_in_place(B, d, N, segments):
 
 @pytest.mark.parametrize("tile", [0, 1, 6, 7, 8, 15, 16, 21])
 def test_width_128_finds_an_infinity_in_any_tile(B, tile):
-    # the walk looks up every eighth tile whether it has to be taken again, and at its end
+    # the walk looks up every second tile whether it has to be taken again, and at its end
     N, col = 700, 77
     q, k, v, gamma = W.make_custom_forward_inputs(1, 2, N, 128, "f32", seed=40 + tile)
     tok = 32 * tile + 16  # the first of a sixteen: earlier tokens of its sixteen would meet it with a weight of zero
