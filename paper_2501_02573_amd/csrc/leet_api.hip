@@ -114,8 +114,10 @@ int f32_pre_split(long BH, int nseg, int seg_chunks) {
 // workgroup) and of its HBM/last-level-cache transfer time; a call is the sum of its kernels plus
 // a fixed cost per call.  The constants are a least-squares fit (5 % rms) to event-timed runs of
 // both kernels at 1 to 64 segments over B*H in 1..768 and N in 256..65536 (each of the three shapes); the tabulated runs are
-// kept with the profiles, and a host test checks the planner's picks against them.  Width 64: the runs of the
-// column-split kernel are from before its third loader stage, which is 4 to 7 % faster where inputs come from memory.
+// kept with the profiles, and a host test checks the planner's picks against them.  They are from before the
+// column-split kernel's third loader stage (width 64) and its Q tile in LDS.  Against the same runs repeated with the kernel as it now is the picks are
+// 0.67 % slower than the best on average (0.24 % on the runs that the fit saw) and 20 % at worst, width 64 with B*H 64 and
+// N 16384 (one segment 199 us, two 166); one more of 262 shapes is beyond 12 %.
 struct CostModel {
     double wide_chunk_us, wide_pre_chunk_us;    // lone wide workgroup: walk and pre-pass per chunk
     double coop_chunk_us, coop_pre_chunk_us;    // column-split workgroups of one sequence, likewise
@@ -781,6 +783,6 @@ int leet_attn_set_decode_store(int mode) {
 
 int leet_attn_get_decode_store(void) { return g_decode_store.load(std::memory_order_relaxed); }
 
-const char* leet_attn_version(void) { return "0.8.0"; }
+const char* leet_attn_version(void) { return "0.8.1"; }
 
 }  // extern "C"
