@@ -19,9 +19,9 @@
 // Range: the bf16 matrix instructions take denormal terms and sums (below 2^-126) as zero, and an infinity leaves
 // x - x0 = NaN.  So the walk watches the smallest nonzero operands and whether its results are finite, and where
 // something is out of range the segment is walked again with fp32 matrix instructions (walk_fp32), whose
-// results stand for every operand.  Ordinary data never does that (nor zeros behind a sequence: B4 H16 N4096, half of it
-// zeros, 252 us); the watching costs some 60 of 690 vector operations
-// a tile (B4 H16 N4096, before the walk overlapped them with MFMAs, 273 -> 282 us; without it q, k ~ 2^-60 with v ~ 2^104
+// results stand for every operand.  Ordinary data never does that (nor zeros behind a sequence: B4 H16 N4096 261 us, half of it
+// zeros 247; all out of range 325, an infinity in one sequence 344 to 441 by its place); the watching costs some 60 of 650 vector
+// operations a tile (B4 H16 N4096, before the walk overlapped them with MFMAs, 273 -> 282 us; without it q, k ~ 2^-60 with v ~ 2^104
 // came out with errors of 6e-4).
 //
 // Work split: a column tile of 32 value columns belongs to two waves (in the pre-pass: one),
@@ -31,16 +31,18 @@
 // phases overlap by themselves).
 //
 // What bounds it: the power of its matrix and vector instructions.  Per 32-token tile there are 624 MFMAs of 32 cycles (of 4
-// SIMDs) and, per wave, some 690 vector operations, most of them splits.  The walk forms an operand while an MFMA that does not
+// SIMDs) and, per wave, some 650 vector operations, most of them splits.  The walk forms an operand while an MFMA that does not
 // need it is running: the next tile's k and q during G4, Gam V during G3, the state's update during G2; each wave of a pair
 // splits its half of V and hands the weighted half to the other through LDS.  Two barriers a tile.  B4 H16 N4096, walk: 349
-// thousand cycles with the phases one after the other and three barriers, 307 so; 183 -> 171 us at the clock of a first
+// thousand cycles with the phases one after the other and three barriers, 307 so (313 with the range looked up every second
+// tile); 183 -> 171 us at the clock of a first
 // run.  In a steady run the clock gives way (2.0 -> 1.6 GHz) and a call gains less, 266 -> 254 us; B9 H33 N2000 611 -> 553,
 // B16 H32 N300 122 -> 116.  Before that, against fp32 MFMAs: 319 -> 282, B1 H32 N777 53.5 -> 45.9
 // (walk_fp32 alone, B1 H300 N2000: 805, here 630).
 // Against 64 bits a single product errs by at most 5.99e-8 of itself (5.95e-8 with fp32 MFMAs).  Sums round less
-// often: over forty sizes outputs 0.66e-7..0.95e-7 in the 2-norm (1.5e-7..2.8e-7), states 0.33 to 0.83 of what fp32
-// MFMAs give; the largest single error of a state after two tokens, in units of its rms and over 200 seeds, is 4.2e-7 on
+// often: outputs err 0.30 to 0.47 and states 0.33 to 0.83 as much as with fp32 MFMAs, in the 2-norm over forty sizes; over forty
+// drawn ones (2 to 8000 tokens, with and without decay and entering state) outputs 0.63e-7 to 1.74e-7, states 0.30e-7 to
+// 2.28e-7.  The largest single error of a state after two tokens, in units of its rms and over 200 seeds, is 4.2e-7 on
 // average (5.3e-7) and 8.4e-7 at worst (6.7e-7).
 //
 // MFMA conventions: an A (B) operand of 32x32x16 (16x16x32) holds, in lane l, row (column) l%32
