@@ -50,7 +50,7 @@
 // What bounds it over inputs that come from memory (B4 H16 N4096, width 128, 77 us): a compute unit's loads return in
 // order and only some 50 KB of them can be in flight, so the slices' shared reads of Q and K cost their full latency in
 // every slice: the same 201 MB take 51 us in this placement and 32 us where each compute unit reads a part of its own
-// (stores alone 25 us, no loads 27, all without compute 73).  For the same reason a load that warms L2 for the other slices
+// (stores alone 25 us, no loads 27, all without compute 73; parts switched off while Q ran three chunks ahead).  For the same reason a load that warms L2 for the other slices
 // holds up its own compute unit's loads behind it and gains nothing, and neither do more stages.
 //
 // MFMA conventions (32x32x16): an A (B) operand holds, in lane l, row (column) l%32 and the
